@@ -15,6 +15,7 @@
 // MODE = 1 the pass also completes the fixed-point iteration of each link as soon as its
 // force is complete (E' = Ebase + dt f1, under-relaxed, new trial link), so the force is
 // never stored; MODE = 0 stores f1 (the per-step term f1(U(t), U(t - dt))).
+#include <algorithm>
 #include "internal.h"
 #include "stencil.h"
 
@@ -189,12 +190,9 @@ template <typename A> __device__ __forceinline__ A add2(const A& x, const A& y) 
 
 }  // namespace
 
-// Layers per chunk of the march: every chunk repeats the loops of the layer before it to
-// start its carries (1 / MARCH_LZ extra work) and chunks give the launch its parallelism.
-#ifndef GL_MARCH_LZ
-#define GL_MARCH_LZ 16
-#endif
 constexpr int MARCH_BS = 256;
+// micro-steps of a layer, and of the layer before a chunk (its carries)
+constexpr int MARCH_SUB = 21, MARCH_WARM = 6;
 // The five long-lived accumulators (derivatives of the site's three links, carries to two
 // links of the next layer) sit in per-thread LDS slots, 5 n_g reals per thread: 80 KB per
 // work-group for SU(3) in double precision, two work-groups per CU.  Held in registers
@@ -226,7 +224,7 @@ __device__ __forceinline__ void atomic_max_nn(double* addr, double v) {
 
 template <typename G, typename T, int MODE>
 __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(GL_MARCH_WAVES))) k_semi_march(const T* __restrict__ A, const T* __restrict__ B, Geom g,
-                                                         StepConst c, MarchIter it, int ncg, int nch) {
+                                                         StepConst c, MarchIter it, int ncg, int nch, int lz) {
   using L = typename G::Link;
   using Ag = typename G::Alg;
   using R = typename G::Real;
@@ -251,8 +249,8 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(G
   Site b0;
   b0.x = t % g.nt;
   b0.y = t / g.nt;
-  const int z0 = ch * GL_MARCH_LZ;
-  const int z1 = min(z0 + GL_MARCH_LZ, g.nz);
+  const int z0 = ch * lz;
+  const int z1 = min(z0 + lz, g.nz);
   const XNbr xn = x_nbr(g, b0);
   const R kxy = (R)(0.5 / (c.a[0] * c.a[0] * c.a[1] * c.a[1]));
   const R kxz = (R)(0.25 / (c.a[0] * c.a[0] * c.a[2] * c.a[2]));
@@ -414,7 +412,7 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(G
   cx.set(G::alg_zero());
   cy.set(G::alg_zero());
   Ag P1 = G::alg_zero(), P2 = G::alg_zero(), snd = G::alg_zero();
-  constexpr int NSUB = 21, NWARM = 6;
+  constexpr int NSUB = MARCH_SUB, NWARM = MARCH_WARM;
   const int zm = z0 > 0 ? z0 - 1 : g.nz - 1;
   const int nq = NWARM + (z1 - z0) * NSUB;
 #pragma unroll 1
@@ -576,17 +574,40 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(G
   }
 }
 
+// Layers per chunk of the march.  A chunk first repeats the loops of the layer before it that
+// feed its carries (MARCH_WARM of the MARCH_SUB micro-steps of a layer), and a wavefront does
+// its micro-steps one after the other, so a launch takes (MARCH_WARM + lz MARCH_SUB) micro-steps
+// for every round of work-groups that the chip holds at once.  The length with the fewest is
+// taken (the longest of equals: less repeated work): 16 layers on 512 x 64 x 64, which fill
+// the chip in one round (8 layers, two rounds: 7% slower), down to single layers where the
+// lattice is too small to fill it: 96 x 32 x 32 FP64, 24 work-groups of 16 layers 0.595 ms per
+// iteration, 384 of one layer 0.109 ms.  The result does not depend on the length
+// (the repeated loops are the same operations on the same links).
+constexpr int MARCH_LZ_MAX = 16;
+inline int march_chunk(int ncg, int nz, int resident) {
+  int best = 1;
+  int64_t best_cost = INT64_MAX;
+  for (int lz = 1; lz <= MARCH_LZ_MAX; ++lz) {
+    const int64_t groups = (int64_t)ncg * ((nz + lz - 1) / lz);
+    const int64_t cost = (groups + resident - 1) / resident * (MARCH_WARM + (int64_t)std::min(lz, nz) * MARCH_SUB);
+    if (cost <= best_cost) { best_cost = cost; best = lz; }
+  }
+  return best;
+}
+
 template <typename G, typename T>
 void launch_semi_march(const T* A, const T* B, const Geom& g, const StepConst& c, int mode, const MarchIter& it,
                        hipStream_t st) {
   const int ncol = (int)(g.layer / 64);
   const int ncg = (ncol + MARCH_BS / 64 - 1) / (MARCH_BS / 64);
-  const int nch = (g.nz + GL_MARCH_LZ - 1) / GL_MARCH_LZ;
+  // work-groups resident at once: two per CU at the kernel's two waves per SIMD, 256 CUs
+  const int lz = march_chunk(ncg, g.nz, 2 * 256);
+  const int nch = (g.nz + lz - 1) / lz;
   const dim3 grid((unsigned)(ncg * nch));
   if (mode == 0)
-    hipLaunchKernelGGL((k_semi_march<G, T, 0>), grid, dim3(MARCH_BS), 0, st, A, B, g, c, it, ncg, nch);
+    hipLaunchKernelGGL((k_semi_march<G, T, 0>), grid, dim3(MARCH_BS), 0, st, A, B, g, c, it, ncg, nch, lz);
   else
-    hipLaunchKernelGGL((k_semi_march<G, T, 1>), grid, dim3(MARCH_BS), 0, st, A, B, g, c, it, ncg, nch);
+    hipLaunchKernelGGL((k_semi_march<G, T, 1>), grid, dim3(MARCH_BS), 0, st, A, B, g, c, it, ncg, nch, lz);
 }
 
 #define GL_MARCH_INST(G, T) \

@@ -309,3 +309,30 @@ def test_full_size_semi_implicit_sampled(hop):
             ref = su.expi(a[i] * p.dt * E_new[i]) @ U0[i, 2, 2, 2]
             assert np.abs(U1[i, 2, 2, 2] - ref).max() < 1e-12
     say("worst sampled E residual (relative to max |E|)", worst)
+
+
+@pytest.mark.parametrize("nc,nt,nz,reps", [(3, 8, 10, 103), (2, 8, 10, 800), (2, 64, 3, 30)])
+def test_march_chunk_lengths_agree(nc, nt, nz, reps):
+    """The marching pass cuts the layers into chunks whose length follows from the lattice's
+    size: nz layers of a state that repeats `reps` times along z (chunks of 3 layers, the
+    last one short; of 16; of 3 over several column groups) against the nz layers alone
+    (chunks of 1).  Same operations on the same links: bitwise equal, through hops."""
+    pkg = lattice_or_skip()
+    w = synth.Workload(f"su{nc}-{nz}x{nt}", nc=nc, nz=nz, nt=nt, dt=1.0, mu=0.5, sigma=1.5, seed=390 + nt)
+    say("case: march chunks", w.name, "x", reps)
+    p, mv = mv_setup(w)
+    rA, rB = synth.mv_charges(w.seed, nc, nt, w.mu, w.a_T)
+    st, _ = init_mv.initial_state(rA, rB, nz, p, mv)
+    arrs = to_comp(st)
+    V = nz * nt * nt
+    one = new_lattice(pkg, w, scheme=1, max_iter=100, tol=1e-12)
+    one.init_state(*arrs, step0=0)
+    many = pkg.Lattice(nc=nc, nz=nz * reps, nt=nt, a_T=w.a_T, a_L=w.a_L, dt=w.dt, fp=64, scheme=1, max_iter=100,
+                       tol=1e-12)
+    many.init_state(*[np.tile(x, reps) for x in arrs], step0=0)
+    one.step(2)
+    many.step(2)
+    a, b = one.get_state(), many.get_state()
+    for k in ("U", "E", "rhoA", "rhoB"):
+        x = b[k].reshape(*b[k].shape[:-1], reps, V)
+        assert np.array_equal(x, np.broadcast_to(a[k][..., None, :], x.shape)), k
