@@ -79,3 +79,30 @@ def test_thin_nuclei_approach_the_boost_invariant_glasma():
     assert peaks[0] < peaks[1] < peaks[2], peaks
     assert abs(peaks[2] - 1.0) < 0.15, peaks
     assert mins[0] > 0.0 and mins[2] < -0.5, mins
+
+
+@pytest.mark.parametrize("nt", [2, 3, 31, 32, 33, 64, 129, 258, 513, 2050])
+def test_transverse_field_sizes(nt):
+    """The DFT passes of the transverse Poisson equation at the edges of their forms: one
+    work-group per plane (up to 32), staged lines (from 33; sums of one, two and three chunks
+    of 256 terms; one and several blocks of outputs), lines beyond the phase table (2050).
+    One colour per nucleus, SU(2): alpha^i_N = 2 sin(d_i phi_N / 2) / a_T in closed form, and
+    E_z^3 is the site average of alpha_A^i alpha_B^i, with phi from numpy's FFT.  Sums of nt
+    terms of rounding 2^-53 each and their products stay far below 1e-11 of the largest."""
+    pkg = lattice_or_skip()
+    print("case: transverse field, nt", nt, flush=True)
+    a_T, m, cut = 4.0, 0.2, 0.6   # |k~| up to 0.71: part of the modes is cut, at nt = 2 one
+    g = synth.rng(500 + nt)
+    rho = np.zeros((2, 3, nt, nt))
+    rho[0, 0], rho[1, 1] = g.standard_normal((2, nt, nt)) * 0.1
+    k2 = init_mv.ktilde2(nt, a_T)
+    filt = np.where(np.sqrt(k2) <= cut, 1.0 / (k2 + m * m), 0.0)
+    phi = [np.real(np.fft.ifft2(np.fft.fft2(rho[n, n]) * filt)) for n in range(2)]
+    ez = np.zeros((nt, nt))
+    for ax in (-1, -2):
+        al = [2.0 * np.sin((np.roll(p, -1, axis=ax) - p) / 2) / a_T for p in phi]
+        ez += 0.5 * (al[0] * al[1] + np.roll(al[0] * al[1], 1, axis=ax))
+    got = pkg.boost_invariant_fields(2, nt, rho[0], rho[1], a_T=a_T, m_ir=m, uv_cut=cut)["Ez"].cpu().numpy()
+    err = np.abs(got[2] - ez).max() / max(np.abs(ez).max(), 1e-300)
+    print("  max error / max", err, flush=True)
+    assert err < 1e-11 and np.abs(got[:2]).max() <= 1e-11 * np.abs(ez).max()
