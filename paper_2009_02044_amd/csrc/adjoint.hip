@@ -9,7 +9,7 @@
 // an anti-hermitian matrix); P(.) of such a product returns its hermitian components.
 //
 // The step  rho' = hop(rho, U);  E' = E + dt (F(U) + j);  U'_i = exp(i c_i E'_i) U_i
-// (c_i = a_i dt) is reversed in three kernels:
+// (c_i = a_i dt) is reversed in three parts:
 //  ra: lam_i <- W^dag lam'_i W,  ebar_i <- ebar'_i + c_i int_0^1 W_s^dag lam'_i W_s ds
 //      (W = exp(i c_i E'_i), W_s = exp(i s c_i E'_i)); ebar then holds dL/dE' = dL/dE.
 //  r1: per plaquette square (corner x, plane (i,j)) the four force terms that contain it,
@@ -17,12 +17,13 @@
 //      hermitian Omega in the frame of W = U_{i,j}(x):
 //        Omega = c_ij [Fbar_i(x) - U_j(x) Fbar_i(x+j) U_j^dag(x)]
 //              - c_ji [Fbar_j(x) - U_i(x) Fbar_j(x+i) U_i^dag(x)],   c_ij = -1/(a_i a_j^2),
-//      and K = P(W i Omega), K' = P(i Omega W) are stored; the two corner links inside the
-//      transports get the extra commutator terms described at k_adj_r1.
-//  r2: each link gathers its four squares: for U_k(y) and m != k, with (i,j) the sorted
-//      plane, +K(y) - U_m^dag K'(y-m) U_m (k = i) or +U_m^dag K(y-m) U_m - K'(y) (k = j),
-//      U_m = U_m(y-m); on hop steps the charge transport adds to lam_z and moves the charge
-//      cotangents back one cell.
+//      and K = P(W i Omega), K' = P(i Omega W) are stored; the corner's own two links get
+//      K, -K' and the derivative of the transports at once (k_adj_r1).
+//  r2: each link gathers the squares whose corner is another site: for U_k(y) and m != k,
+//      -U_m^dag K'(y-m) U_m (k < m) or +U_m^dag K(y-m) U_m (k > m), U_m = U_m(y-m); on hop
+//      steps the charge transport adds to lam_z and moves the charge cotangents back one cell.
+// ra only touches its own link, so r2 of a step goes on with ra of the step before it (k_adj_r2
+// with RA) and ra stands alone only before the first reversed step.
 #include "internal.h"
 #include "stencil.h"
 #include "adjoint.h"
@@ -152,7 +153,6 @@ __global__ void __launch_bounds__(256) k_sum(const double* __restrict__ partial,
 template <typename Gd, typename S>
 __global__ void __launch_bounds__(256) k_adj_ra(const S* __restrict__ E1, Geom g, double ax, double ay, double az,
                                                 double dt, double* __restrict__ lam, double* __restrict__ ebar) {
-  using L = typename Gd::Link;
   using A = typename Gd::Alg;
   Site x;
   uint32_t s;
@@ -163,134 +163,181 @@ __global__ void __launch_bounds__(256) k_adj_ra(const S* __restrict__ E1, Geom g
   load_alg(e, E1, i, s, g.Vp);
   ld(lp, lam, i, g.V, s);
   ld(ep, ebar, i, g.V, s);
-  const L W = Gd::expi(e, c);
-  const A l = Gd::transport(W, lp);
-  axpy(ep, 1.0, dexp_transpose<Gd>(e, c, lp));
+  A l;
+  axpy(ep, 1.0, dexp_reverse<Gd>(e, c, lp, l));
   st(l, lam, i, g.V, s);
   st(ep, ebar, i, g.V, s);
 }
 
 // ---- r1: one hermitian cotangent per plaquette square -------------------------------
-// One thread per site x, the three planes in turn.  Besides K, K' it adds to lam_i(x) and
-// lam_j(x) the derivative of the transports U_j(x) . U_j^dag(x) and U_i(x) . U_i^dag(x)
-// that rotate the terms of F_i(x+j) and F_j(x+i) into the frame of W:
-//   lam_i(x) += P([i T4, W]),  lam_j(x) -= P([i T3, W]),
+// One thread per site x, the three planes in turn.  With W = U_{i,j}(x) = C + i S (C, S
+// hermitian) and components s of S, every derivative is a product of algebra elements:
+//   K  = P(W i Omega) = (sym(C, omega) + cross(omega, s)) / 2,
+//   K' = P(i Omega W) = (sym(C, omega) - cross(omega, s)) / 2.
+// Besides K, K' it adds to lam_i(x) and lam_j(x) the derivative of the transports
+// U_j(x) . U_j^dag(x) and U_i(x) . U_i^dag(x) that rotate the terms of F_i(x+j) and F_j(x+i)
+// into the frame of W:
+//   lam_i(x) += P([i T4, W]) = -cross(T4, s),  lam_j(x) -= P([i T3, W]) = -cross(T3, s),
 //   T3 = dt c_ij U_j(x) ebar_i(x+j) U_j^dag(x),  T4 = dt c_ji U_i(x) ebar_j(x+i) U_i^dag(x).
+// and the corner's own shares lam_i(x) += K, lam_j(x) -= K'.  On hop steps (rA not null) it also
+// completes the cotangent of the hopped charge, rbarA'(x) += a_L ebar_z(x), which r2 reads at
+// the neighbours too.
+// Bound by memory: 1.1 KB per site, 3.9 TB/s at 256 x 32 x 32 (half of it writes).  lam is read
+// and written once per link, its sums held in LDS, and the order of the terms keeps the
+// unrolled planes at two waves per SIMD (242 registers; sums in registers: 358, one wave).  88 us
+// with the products formed as matrices and lam read and written per plane, 75 us now.  One
+// loop body for the planes instead of three: 81 us.
 template <typename Gd, typename S>
-__global__ void __launch_bounds__(256) k_adj_r1(const S* __restrict__ U, Geom g, double ax, double ay, double az,
+__global__ void __launch_bounds__(256, 2) k_adj_r1(const S* __restrict__ U, Geom g, double ax, double ay, double az,
                                                 double dt, const double* __restrict__ ebar, double* __restrict__ K,
-                                                double* __restrict__ lam) {
+                                                double* __restrict__ lam, double* __restrict__ rA) {
   using L = typename Gd::Link;
   using A = typename Gd::Alg;
+  using Op = AdjOps<Gd>;
   constexpr int NG = Gd::NG;
   Site x;
   uint32_t s;
   if (!site_of(g, blockIdx.x, gridDim.x, threadIdx.x, blockDim.x, x, s)) return;
-  const double a[3] = {ax, ay, az};
-#pragma unroll 1
+  // the sums for lam in per-thread LDS slots (a thread only touches its own)
+  __shared__ double acc[3 * NG * 256];
+  double* l = acc + threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < 3 * NG; ++q) l[q * 256] = 0.0;
+#pragma unroll
   for (int p = 0; p < 3; ++p) {              // plane (0,1), (0,2), (1,2)
     const int i = p == 2 ? 1 : 0, j = p == 0 ? 1 : 2;
-    const double cij = -dt / (a[i] * a[j] * a[j]), cji = -dt / (a[j] * a[i] * a[i]);
+    const double ai = i == 0 ? ax : ay, aj = j == 1 ? ay : az;
+    const double cij = -dt / (ai * aj * aj), cji = -dt / (aj * ai * ai);
     const Site xpi = shifted(g, x, i, +1), xpj = shifted(g, x, j, +1);
-    L Ui, Uj, Ujpi, Uipj;
+    L Ui, Uj;
+    double c0;
+    A cw, sw, t, om;
     load_link(Ui, U, i, s, g.Vp);
     load_link(Uj, U, j, s, g.Vp);
-    load_link(Ujpi, U, j, idx(g, xpi), g.Vp);
-    load_link(Uipj, U, i, idx(g, xpj), g.Vp);
-    A ei, ej, t3, t4;
-    ld(ei, ebar, i, g.V, s);
-    ld(ej, ebar, j, g.V, s);
-    ld(t3, ebar, i, g.V, idx(g, xpj));
-    t3 = Gd::transport_inv(Uj, t3);
-    ld(t4, ebar, j, g.V, idx(g, xpi));
-    t4 = Gd::transport_inv(Ui, t4);
-    A om;
-    for (int k = 0; k < NG; ++k) {
-      t3.c[k] *= cij;
-      t4.c[k] *= cji;
-      om.c[k] = cij * ei.c[k] - cji * ej.c[k] - t3.c[k] + t4.c[k];
+    {
+      L Ujpi, Uipj;
+      load_link(Ujpi, U, j, idx(g, xpi), g.Vp);
+      load_link(Uipj, U, i, idx(g, xpj), g.Vp);
+      Op::split(Gd::mul_dag(Gd::mul_dag(Gd::mul(Ui, Ujpi), Uipj), Uj), c0, cw, sw);
     }
-    const L W = Gd::mul_dag(Gd::mul_dag(Gd::mul(Ui, Ujpi), Uipj), Uj);
-    const L Oh = AdjOps<Gd>::anti(om);
-    st(Gd::proj(Gd::mul(W, Oh)), K, 2 * p, g.V, s);
-    st(Gd::proj(Gd::mul(Oh, W)), K, 2 * p + 1, g.V, s);
-    A l;
-    ld(l, lam, i, g.V, s);
-    axpy(l, 1.0, Gd::proj(commut<Gd>(AdjOps<Gd>::anti(t4), W)));
-    st(l, lam, i, g.V, s);
-    ld(l, lam, j, g.V, s);
-    axpy(l, -1.0, Gd::proj(commut<Gd>(AdjOps<Gd>::anti(t3), W)));
-    st(l, lam, j, g.V, s);
+    staple_fence<true>();
+    ld(om, ebar, i, g.V, s);
+    ld(t, ebar, j, g.V, s);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) om.c[k] = cij * om.c[k] - cji * t.c[k];
+    ld(t, ebar, i, g.V, idx(g, xpj));
+    t = Gd::transport_inv(Uj, t);                           // T3 / c_ij
+    axpy(om, -cij, t);
+    {
+      const A z = Op::cross(t, sw);                         // lam_j -= -cross(T3, s)
+#pragma unroll
+      for (int k = 0; k < NG; ++k) l[(j * NG + k) * 256] += cij * z.c[k];
+    }
+    ld(t, ebar, j, g.V, idx(g, xpi));
+    t = Gd::transport_inv(Ui, t);                           // T4 / c_ji
+    axpy(om, cji, t);
+    {
+      const A z = Op::cross(t, sw);                         // lam_i += -cross(T4, s)
+#pragma unroll
+      for (int k = 0; k < NG; ++k) l[(i * NG + k) * 256] -= cji * z.c[k];
+    }
+    const A d = Op::sym(c0, cw, om), z = Op::cross(om, sw);
+    A k0, k1;
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+      k0.c[k] = 0.5 * (d.c[k] + z.c[k]);
+      k1.c[k] = 0.5 * (d.c[k] - z.c[k]);
+    }
+    st(k0, K, 2 * p, g.V, s);
+    st(k1, K, 2 * p + 1, g.V, s);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+      l[(i * NG + k) * 256] += k0.c[k];
+      l[(j * NG + k) * 256] -= k1.c[k];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    A t;
+    ld(t, lam, i, g.V, s);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) t.c[k] += l[(i * NG + k) * 256];
+    st(t, lam, i, g.V, s);
+  }
+  if (rA) {
+    A t, ez;
+    ld(t, rA, 0, g.V, s);
+    ld(ez, ebar, 2, g.V, s);
+    axpy(t, az, ez);
+    st(t, rA, 0, g.V, s);
   }
 }
 
-// ---- r2: gather of the link cotangents; hop reverse ---------------------------------
-// Charges: rho_A at state s+1 in co-moving slots with offset offA1, rho_B at state s with
-// offset offB0.
-template <typename Gd, typename S, bool HOP>
-__global__ void __launch_bounds__(256) k_adj_r2(const S* __restrict__ U, const S* __restrict__ rhoA1,
-                                                const S* __restrict__ rhoB0, int offA1, int offB0, Geom g, double aL,
-                                                const double* __restrict__ ebar, const double* __restrict__ K,
+// ---- r2: gather of the link cotangents; hop reverse; ra of the step before -----------
+// One thread per link (blockIdx.y).  Charges: rho_A at state s+1 in co-moving slots with
+// offset offA1, rho_B at state s with offset offB0; rAin holds rbarA' + a_L ebar_z (r1).
+// With RA, E0 is the field of state s, the E' of the step before.  Bound by memory; the joined
+// form reads and writes lam once less per step (apart: r2 52 / 79 us without / with a hop and
+// ra 38 us at 256 x 32 x 32, joined 66 / 84 us).
+template <typename Gd, typename S, bool HOP, bool RA>
+__global__ void __launch_bounds__(256) k_adj_r2(const S* __restrict__ U, const S* __restrict__ E0,
+                                                const S* __restrict__ rhoA1, const S* __restrict__ rhoB0, int offA1,
+                                                int offB0, Geom g, double aT, double aL, double dt,
+                                                double* __restrict__ ebar, const double* __restrict__ K,
                                                 double* __restrict__ lam, const double* __restrict__ rAin,
                                                 const double* __restrict__ rBin, double* __restrict__ rAout,
                                                 double* __restrict__ rBout) {
   using L = typename Gd::Link;
   using A = typename Gd::Alg;
-  constexpr int NG = Gd::NG;
   Site y;
   uint32_t s;
   if (!site_of(g, blockIdx.x, gridDim.x, threadIdx.x, blockDim.x, y, s)) return;
-  for (int k = 0; k < 3; ++k) {
-    A acc, t;
-    ld(acc, lam, k, g.V, s);
-    for (int m = 0; m < 3; ++m) {
-      if (m == k) continue;
-      const int p = k + m - 1;
-      const uint32_t sm = idx(g, shifted(g, y, m, -1));
-      L Um;
-      load_link(Um, U, m, sm, g.Vp);
-      if (k < m) {
-        ld(t, K, 2 * p, g.V, s);
-        axpy(acc, 1.0, t);
-        ld(t, K, 2 * p + 1, g.V, sm);
-        axpy(acc, -1.0, Gd::transport(Um, t));
-      } else {
-        ld(t, K, 2 * p, g.V, sm);
-        axpy(acc, 1.0, Gd::transport(Um, t));
-        ld(t, K, 2 * p + 1, g.V, s);
-        axpy(acc, -1.0, t);
-      }
-    }
-    if (HOP && k == 2) {
-      L Uz;
-      load_link(Uz, U, 2, s, g.Vp);
-      A abar, ez, ra1, rb0, bin;
-      ld(abar, rAin, 0, g.V, s);
-      ld(ez, ebar, 2, g.V, s);
-      axpy(abar, aL, ez);                                   // dL/drho_A'(y)
-      load_alg(ra1, rhoA1, 0, site_index(g, y.x, y.y, slotA(y.z, offA1, g.nz)), g.Vp);
-      load_alg(rb0, rhoB0, 0, site_index(g, y.x, y.y, slotB(y.z, offB0, g.nz)), g.Vp);
-      ld(bin, rBin, 0, g.V, idx(g, shifted(g, y, 2, +1)));
-      A R = Gd::transport_inv(Uz, bin);                     // U_z(y) rbarB'(y+z) U_z^dag(y)
-      axpy(acc, 1.0, Gd::proj(commut<Gd>(AdjOps<Gd>::anti(ra1), AdjOps<Gd>::anti(abar))));
-      axpy(acc, 1.0, Gd::proj(commut<Gd>(AdjOps<Gd>::anti(R), AdjOps<Gd>::anti(rb0))));
-      axpy(R, -aL, ez);
-      st(R, rBout, 0, g.V, s);
-    }
-    st(acc, lam, k, g.V, s);
+  const int k = blockIdx.y;
+  A acc, t;
+  ld(acc, lam, k, g.V, s);
+#pragma unroll 1
+  for (int q = 0; q < 2; ++q) {
+    const int m = q == 0 ? (k == 0 ? 1 : 0) : (k == 2 ? 1 : 2);   // the two directions other than k
+    const int p = k + m - 1;
+    const uint32_t sm = idx(g, shifted(g, y, m, -1));
+    L Um;
+    load_link(Um, U, m, sm, g.Vp);
+    ld(t, K, k < m ? 2 * p + 1 : 2 * p, g.V, sm);
+    axpy(acc, k < m ? -1.0 : 1.0, Gd::transport(Um, t));
   }
-  if (HOP) {
+  A ek;
+  if (RA || HOP) ld(ek, ebar, k, g.V, s);
+  if (HOP && k == 2) {
+    L Uz;
+    load_link(Uz, U, 2, s, g.Vp);
+    A abar, ra1, rb0, bin;
+    ld(abar, rAin, 0, g.V, s);                              // dL/drho_A'(y)
+    load_alg(ra1, rhoA1, 0, site_index(g, y.x, y.y, slotA(y.z, offA1, g.nz)), g.Vp);
+    load_alg(rb0, rhoB0, 0, site_index(g, y.x, y.y, slotB(y.z, offB0, g.nz)), g.Vp);
+    ld(bin, rBin, 0, g.V, idx(g, shifted(g, y, 2, +1)));
+    A R = Gd::transport_inv(Uz, bin);                       // U_z(y) rbarB'(y+z) U_z^dag(y)
+    axpy(acc, -1.0, AdjOps<Gd>::cross(ra1, abar));
+    axpy(acc, -1.0, AdjOps<Gd>::cross(R, rb0));
+    axpy(R, -aL, ek);
+    st(R, rBout, 0, g.V, s);
+  }
+  if (HOP && k == 0) {
     // rbarA(y) = U_z^dag(y-z) [rbarA'(y-z) + a_L ebar_z(y-z)] U_z(y-z)
     const uint32_t sm = idx(g, shifted(g, y, 2, -1));
     L Uz;
     load_link(Uz, U, 2, sm, g.Vp);
-    A abar, ez;
+    A abar;
     ld(abar, rAin, 0, g.V, sm);
-    ld(ez, ebar, 2, g.V, sm);
-    axpy(abar, aL, ez);
     st(Gd::transport(Uz, abar), rAout, 0, g.V, s);
   }
-  (void)NG;
+  if constexpr (RA) {
+    A e, l;
+    load_alg(e, E0, k, s, g.Vp);
+    axpy(ek, 1.0, dexp_reverse<Gd>(e, (k == 2 ? aL : aT) * dt, acc, l));
+    st(ek, ebar, k, g.V, s);
+    acc = l;
+  }
+  st(acc, lam, k, g.V, s);
 }
 
 // ---- device state transfer (plain double arrays <-> tiled storage) --------------------
@@ -406,19 +453,25 @@ void launch_adj_loss(const S* U, const S* E, const Geom& g, const double* a, int
 size_t adj_loss_partials(const Geom& g) { return nblocks(g); }
 
 template <typename G, typename S>
-void launch_adj_step(const S* U0, const S* E1, const S* rhoA1, const S* rhoB0, int offA1, int offB0, bool hop,
-                     const Geom& g, const double* a, double dt, double* lam, double* ebar, double* K,
-                     const double* rAin, const double* rBin, double* rAout, double* rBout, hipStream_t stm) {
+void launch_adj_ra(const S* E1, const Geom& g, const double* a, double dt, double* lam, double* ebar,
+                   hipStream_t stm) {
+  using Gd = typename GroupOf<G::NC, double>::type;
+  hipLaunchKernelGGL((k_adj_ra<Gd, S>), dim3(nblocks(g), 3), dim3(256), 0, stm, E1, g, a[0], a[1], a[2], dt, lam, ebar);
+}
+template <typename G, typename S>
+void launch_adj_step(const S* U0, const S* E0, const S* rhoA1, const S* rhoB0, int offA1, int offB0, bool hop,
+                     bool more, const Geom& g, const double* a, double dt, double* lam, double* ebar, double* K,
+                     double* rAin, const double* rBin, double* rAout, double* rBout, hipStream_t stm) {
   using Gd = typename GroupOf<G::NC, double>::type;
   const unsigned nb = nblocks(g);
-  hipLaunchKernelGGL((k_adj_ra<Gd, S>), dim3(nb, 3), dim3(256), 0, stm, E1, g, a[0], a[1], a[2], dt, lam, ebar);
-  hipLaunchKernelGGL((k_adj_r1<Gd, S>), dim3(nb), dim3(256), 0, stm, U0, g, a[0], a[1], a[2], dt, ebar, K, lam);
-  if (hop)
-    hipLaunchKernelGGL((k_adj_r2<Gd, S, true>), dim3(nb), dim3(256), 0, stm, U0, rhoA1, rhoB0, offA1, offB0, g, a[2],
+  hipLaunchKernelGGL((k_adj_r1<Gd, S>), dim3(nb), dim3(256), 0, stm, U0, g, a[0], a[1], a[2], dt, ebar, K, lam,
+                     hop ? rAin : nullptr);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nb, 3), dim3(256), 0, stm, U0, E0, rhoA1, rhoB0, offA1, offB0, g, a[0], a[2], dt,
                        ebar, K, lam, rAin, rBin, rAout, rBout);
-  else
-    hipLaunchKernelGGL((k_adj_r2<Gd, S, false>), dim3(nb), dim3(256), 0, stm, U0, rhoA1, rhoB0, offA1, offB0, g,
-                       a[2], ebar, K, lam, rAin, rBin, rAout, rBout);
+  };
+  if (hop) more ? go(k_adj_r2<Gd, S, true, true>) : go(k_adj_r2<Gd, S, true, false>);
+  else more ? go(k_adj_r2<Gd, S, false, true>) : go(k_adj_r2<Gd, S, false, false>);
 }
 
 template <typename G, typename S>
@@ -453,9 +506,10 @@ void launch_amp(const double* rbar, const double* base, const S* rho, int off, i
 #define GL_ADJ_INST(G, S)                                                                                          \
   template void launch_adj_loss<G, S>(const S*, const S*, const Geom&, const double*, int, int, double, double*,  \
                                       double*, double*, double*, double*, double*, hipStream_t);                  \
-  template void launch_adj_step<G, S>(const S*, const S*, const S*, const S*, int, int, bool, const Geom&,        \
-                                      const double*, double, double*, double*, double*, const double*,            \
-                                      const double*, double*, double*, hipStream_t);                              \
+  template void launch_adj_ra<G, S>(const S*, const Geom&, const double*, double, double*, double*, hipStream_t);   \
+  template void launch_adj_step<G, S>(const S*, const S*, const S*, const S*, int, int, bool, bool, const Geom&,   \
+                                      const double*, double, double*, double*, double*, double*, const double*,   \
+                                      double*, double*, hipStream_t);                                              \
   template void launch_pack<G, S>(const double*, const double*, S*, const Geom&, int, int, hipStream_t);          \
   template void launch_unpack<G, S>(const S*, double*, const Geom&, int, int, int, int, hipStream_t);             \
   template void launch_pack_links<G, S>(const double*, S*, const Geom&, hipStream_t);                             \

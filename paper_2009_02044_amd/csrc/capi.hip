@@ -765,7 +765,8 @@ static void host_op(int op, int64_t n, const double* in, double* out) {
         using Gd = typename GroupOf<G::NC, double>::type;
         typename Gd::Alg e, l;
         for (int k = 0; k < NG; ++k) { e.c[k] = in[1 + k]; l.c[k] = in[1 + NG + k]; }
-        const typename Gd::Alg r = dexp_transpose<Gd>(e, in[0], l);
+        typename Gd::Alg moved;
+        const typename Gd::Alg r = dexp_reverse<Gd>(e, in[0], l, moved);
         for (int k = 0; k < NG; ++k) out[k] = r.c[k];
         in += 1 + 2 * NG;
         out += NG;
@@ -1314,6 +1315,7 @@ static int adjoint_reverse(glasma_ctx* c, void* work, size_t work_bytes, Seed&& 
     int r = seed.template operator()<G, T>(fin, lam, ebar, rA[0], rB[0], part);
     if (r) return r;
     const size_t nE = 3 * (size_t)c->ng * c->g.Vp * sizeof(T), nR = (size_t)c->ng * c->g.Vp * sizeof(T);
+    if (steps > 0) launch_adj_ra<G, T>((const T*)fin.E, c->g, sp, c->p.dt, lam, ebar, c->stream);
     for (int64_t k = a.nseg - 1; k >= 0; --k) {
       const int64_t sk = s0 + k * every;
       const int64_t len = std::min<int64_t>(every, steps - k * every);
@@ -1341,9 +1343,9 @@ static int adjoint_reverse(glasma_ctx* c, void* work, size_t work_bytes, Seed&& 
         const int64_t s = sk + m;
         const StatePtr x = slot(m), y = slot(m + 1);
         const bool hop = is_hop(c, s);
-        launch_adj_step<G, T>((const T*)x.U, (const T*)y.E, (const T*)y.rA, (const T*)x.rB,
-                              off_at(c, s0, off0, s + 1), off_at(c, s0, off0, s), hop, c->g, sp, c->p.dt, lam, ebar,
-                              K, rA[cur], rB[cur], rA[cur ^ 1], rB[cur ^ 1], c->stream);
+        launch_adj_step<G, T>((const T*)x.U, (const T*)x.E, (const T*)y.rA, (const T*)x.rB,
+                              off_at(c, s0, off0, s + 1), off_at(c, s0, off0, s), hop, s > s0, c->g, sp, c->p.dt,
+                              lam, ebar, K, rA[cur], rB[cur], rA[cur ^ 1], rB[cur ^ 1], c->stream);
         if (hop) cur ^= 1;
       }
     }

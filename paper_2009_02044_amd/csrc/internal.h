@@ -176,13 +176,17 @@ size_t adj_loss_partials(const Geom& g);
 template <typename G, typename S>
 void launch_adj_loss(const S* U, const S* E, const Geom& g, const double* a, int z0, int z1, double scale,
                      double* lam, double* ebar, double* rA, double* rB, double* partial, double* out, hipStream_t st);
-// One reverse step: state s (U0, rhoB0 at offset offB0), E1 and rhoA1 (offset offA1) of
-// state s + 1; K holds 6 n_g V doubles; on hop steps the charge cotangents move from
-// (rAin, rBin) to (rAout, rBout).
+// Reverse of the link update whose new field is E1 (before the first reversed step).
 template <typename G, typename S>
-void launch_adj_step(const S* U0, const S* E1, const S* rhoA1, const S* rhoB0, int offA1, int offB0, bool hop,
-                     const Geom& g, const double* a, double dt, double* lam, double* ebar, double* K,
-                     const double* rAin, const double* rBin, double* rAout, double* rBout, hipStream_t st);
+void launch_adj_ra(const S* E1, const Geom& g, const double* a, double dt, double* lam, double* ebar, hipStream_t st);
+// The rest of one reverse step: state s (U0, rhoB0 at offset offB0), rhoA1 (offset offA1) of
+// state s + 1; K holds 6 n_g V doubles; on hop steps the charge cotangents move from
+// (rAin, rBin) to (rAout, rBout), rAin being changed.  more: also the reverse of the link
+// update of the step before, E0 being the field of state s.
+template <typename G, typename S>
+void launch_adj_step(const S* U0, const S* E0, const S* rhoA1, const S* rhoB0, int offA1, int offB0, bool hop,
+                     bool more, const Geom& g, const double* a, double dt, double* lam, double* ebar, double* K,
+                     double* rAin, const double* rBin, double* rAout, double* rBout, hipStream_t st);
 template <typename G, typename S>
 void launch_pack(const double* src, const double* amp, S* dst, const Geom& g, int ndir, int width, hipStream_t st);
 template <typename G, typename S>

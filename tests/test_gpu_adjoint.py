@@ -373,3 +373,27 @@ def test_general_cotangent_against_oracle_jvp(nc):
     say(f"  second observable: GPU {lhs:.12e} oracle JVP {jvp:.12e}")
     assert abs(lhs - jvp) <= 1e-10 * abs(jvp)
     assert np.all(g2["dU0"] == g2["dU0"])                  # finite output
+
+
+@pytest.mark.parametrize("nc,scale", [(2, 0.3), (3, 0.12), (3, 0.3), (3, 1.5)])
+def test_gradient_with_strong_fields(nc, scale):
+    """Fields whose link update |a dt E| lies below, around and above the bound where the
+    reverse of the exponential changes from its series alone to halvings and doublings (the
+    norm bound 2 |c E| crosses 1 within the lattice, and reaches about 12), single-step
+    segments: directional derivatives against the oracle to 1e-10, as for weak fields."""
+    pkg = lattice_or_skip()
+    nz, nt, steps, every, z0, z1 = 6, 4, 3, 1, 2, 4
+    say(f"case: adjoint strong fields nc={nc} scale={scale}")
+    from oracle import su
+    st = small_state(nc, nz, nt, seed=640 + nc)
+    ng, V = nc * nc - 1, nz * nt * nt
+    st.E = su.from_components(synth.normal(641, (3, nz, nt, nt, ng), scale), nc)
+    _, g = gpu_grad(pkg, st, nz, nt, steps, every, z0, z1)
+    for k in range(4):
+        vE = synth.normal(650 + k, (3, ng, V), 1.0)
+        vA, vB = synth.normal(660 + k, (ng, V), 1.0), synth.normal(670 + k, (ng, V), 1.0)
+        got = np.sum(g["dE0"] * vE) + np.sum(g["drhoA0"] * vA) + np.sum(g["drhoB0"] * vB)
+        ref = oracle_dir(st, vE, vA, vB, steps, z0, z1)[1]
+        size = np.sqrt(np.sum(g["dE0"] ** 2) + np.sum(g["drhoA0"] ** 2) + np.sum(g["drhoB0"] ** 2))
+        say(" ", got, ref, abs(got - ref) / size)
+        assert abs(got - ref) < 1e-10 * size, (k, got, ref)
