@@ -310,7 +310,7 @@ int glasma_init_mv_sheets(glasma_ctx* c, const glasma_mv* mv, int32_t ns, const 
       launch_semi_begin<G, T>((T*)c->b.U, (T*)c->b.E, (const T*)nullptr, (const T*)nullptr, (T*)(w + r.up),
                               (T*)(w + r.ut), (T*)(w + r.et), c->g, sc,
                               c->stream);
-      launch_semi_f1<G, T>((T*)c->b.U, (T*)(w + r.up), (T*)(w + r.f2), c->g, sc, c->stream);
+      launch_semi_f1<G, T>((T*)c->b.U, (T*)(w + r.up), (T*)(w + r.f2), c->g, sc, c->stream, (T*)(w + r.cache));
       launch_gauss_charges<G, T>((T*)c->b.U, (T*)c->b.E, (T*)(w + r.f2), c->p.dt, (T*)c->b.rhoA,
                                  (T*)c->b.rhoB, c->g, sc, c->stream);
     }

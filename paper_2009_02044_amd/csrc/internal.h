@@ -94,11 +94,11 @@ template <typename G, typename T>
 void launch_reunit(T* U, const Geom& g, hipStream_t st);
 
 // Semi-implicit scheme (semi.hip)
-// f1(Uc, Uo) of every link into out; cache (may be null): the marching pass also stores
-// the loops of Uc alone there for the iterations of the step
+// f1(Uc, Uo) of every link into out; cache (march_cache_elems reals; unused where the marching
+// pass does not serve the lattice): it also stores the loops of Uc alone for the iterations
 template <typename G, typename T>
 void launch_semi_f1(const T* Uc, const T* Uo, T* out, const Geom& g, const StepConst& c, hipStream_t st,
-                    T* cache = nullptr);
+                    T* cache);
 template <typename G, typename T>
 void launch_semi_begin(const T* U, const T* E, const T* Ep, const T* J, T* Up, T* Ut, T* Et, const Geom& g,
                        const StepConst& c, hipStream_t st);
@@ -130,9 +130,10 @@ struct MarchIter {
   const double* conv_prev;
   double tol, omega;
   void* F;
-  void* cache;   // loops of slice A alone: written by mode 0 (if not null), read by mode 1
+  void* cache;   // C_xy loops of slice A alone: written by mode 0, read by mode 1
+  double k[3], ma[3], madt[3];   // k / 2 of the three planes, -a_d, -a_d dt (set by the launch)
 };
-// elements of the loop cache: 3 planes of full matrices (18 or 4 reals) per padded site
+// elements of the loop cache: one matrix in the stored form of a link per padded site
 size_t march_cache_elems(const Geom& g, int nc);
 bool march_geometry(const Geom& g);
 template <typename G, typename T>

@@ -10,8 +10,8 @@
 //   * links at x + e_z (factor 2 of an (x, z) or (y, z) loop): carried to the next layer;
 //   * links at x + e_y (factor 2 of an (x, y) loop, factor 1 of a (y, z) loop): the site
 //     above forms those loops again at its base - e_y (another wavefront's column).
-// Per site and slice 11 distinct links are read (against about 75 when every link forms
-// all its loops), and about 85 matrix products are formed (against about 135).  With
+// Per site and layer 32 links are loaded (against about 150 when every link forms all its
+// loops), and 71 matrix products are formed (against about 135).  With
 // MODE = 1 the pass also completes the fixed-point iteration of each link as soon as its
 // force is complete (E' = Ebase + dt f1, under-relaxed, new trial link), so the force is
 // never stored; MODE = 0 stores f1 (the per-step term f1(U(t), U(t - dt))).
@@ -28,15 +28,6 @@ template <typename G> __device__ __forceinline__ typename G::Alg hsum(const type
   typename G::Link h = m;
   G::add_to(h, G::dag(m), (typename G::Real)(G::NC == 3 ? 1 : -1));
   return G::alg_from_herm(h);
-}
-template <typename G> __device__ __forceinline__ typename G::Link yP(const typename G::Link& c) {
-  return G::herm_from_alg(G::proj(c));
-}
-// loop F0 F1 F2^dag F3^dag
-template <typename G>
-__device__ __forceinline__ typename G::Link loop4(const typename G::Link& f0, const typename G::Link& f1,
-                                                  const typename G::Link& f2, const typename G::Link& f3) {
-  return G::mul_dag(G::mul_dag(G::mul(f0, f1), f2), f3);
 }
 template <typename A, typename R> __device__ __forceinline__ void axpy(A& acc, R s, const A& x) {
   constexpr int NG = sizeof(acc.c) / sizeof(acc.c[0]);
@@ -112,50 +103,8 @@ __device__ __forceinline__ Alg2<R> hs_herm(const Q2<R>& C, const Alg2<R>& y) {
   return hsum<G>(LEFT ? G::mul(Y, C) : G::mul(C, Y));
 }
 
-// Full matrices in 18-wide records (the loop cache): component 2 (3 r + k) + {re, im}; SU(2)
-// loops are quaternions (4 wide).
-template <typename L> struct FullWidth;
-template <typename R> struct FullWidth<M3<R>> { static constexpr int value = 18; };
-template <typename R> struct FullWidth<Q2<R>> { static constexpr int value = 4; };
-template <typename R, typename T>
-__device__ __forceinline__ void store_full(const M3<R>& m, T* f, int plane, uint32_t s, int64_t Vp) {
-  R v[18];
-#pragma unroll
-  for (int r = 0; r < 3; ++r)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { v[2 * (3 * r + k)] = m.re[r][k]; v[2 * (3 * r + k) + 1] = m.im[r][k]; }
-  store_comps<R, T, 18>(v, field_dir(f, plane, 18, Vp), s);
-}
-template <typename R, typename T>
-__device__ __forceinline__ void store_full(const Q2<R>& m, T* f, int plane, uint32_t s, int64_t Vp) {
-  store_comps<R, T, 4>(m.q, field_dir(f, plane, 4, Vp), s);
-}
-template <typename R, typename T>
-__device__ __forceinline__ void load_full(M3<R>& m, const T* f, int plane, uint32_t s, int64_t Vp) {
-  R v[18];
-  load_comps<R, T, 18>(v, field_dir(f, plane, 18, Vp), s);
-#pragma unroll
-  for (int r = 0; r < 3; ++r)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { m.re[r][k] = v[2 * (3 * r + k)]; m.im[r][k] = v[2 * (3 * r + k) + 1]; }
-}
-template <typename R, typename T>
-__device__ __forceinline__ void load_full(Q2<R>& m, const T* f, int plane, uint32_t s, int64_t Vp) {
-  load_comps<R, T, 4>(m.q, field_dir(f, plane, 4, Vp), s);
-}
-// Accumulator of an algebra element that lives in registers (LDS = false) or in a
-// per-thread slot of the work-group's LDS (LDS = true; a thread only touches its own slot,
-// so no barrier is needed): components k at p[k * MARCH_BS].
-template <typename Ag, typename R, bool LDS> struct Acc;
-template <typename Ag, typename R> struct Acc<Ag, R, false> {
-  Ag v;
-  __device__ __forceinline__ Ag get() const { return v; }
-  __device__ __forceinline__ void set(const Ag& x) { v = x; }
-  __device__ __forceinline__ void add(R s, const Ag& x) { axpy(v, s, x); }
-  __device__ __forceinline__ void scale(R s) {
-    for (int k = 0; k < (int)(sizeof(v.c) / sizeof(v.c[0])); ++k) v.c[k] *= s;
-  }
-};
+// Algebra element in a per-thread slot of the work-group's LDS (a thread only touches its
+// own slot, so no barrier is needed): components k at p[k * BS].
 template <int BS, typename Ag, typename R> struct AccL {
   R* p;
   static constexpr int NG = sizeof(Ag::c) / sizeof(R);
@@ -173,58 +122,49 @@ template <int BS, typename Ag, typename R> struct AccL {
 #pragma unroll
     for (int k = 0; k < NG; ++k) p[k * BS] = fmx(s, x.c[k], p[k * BS]);
   }
-  __device__ __forceinline__ void scale(R s) {
-#pragma unroll
-    for (int k = 0; k < NG; ++k) p[k * BS] *= s;
-  }
 };
 template <typename R> __device__ __forceinline__ R link_token(const M3<R>& m) { return m.re[2][2]; }
 template <typename R> __device__ __forceinline__ R link_token(const Q2<R>& m) { return m.q[3]; }
-template <typename A> __device__ __forceinline__ A add2(const A& x, const A& y) {
-  constexpr int NG = sizeof(x.c) / sizeof(x.c[0]);
-  A r;
-#pragma unroll
-  for (int k = 0; k < NG; ++k) r.c[k] = x.c[k] + y.c[k];
-  return r;
-}
 
 }  // namespace
 
 constexpr int MARCH_BS = 256;
-// micro-steps of a layer, and of the layer before a chunk (its carries)
-constexpr int MARCH_SUB = 21, MARCH_WARM = 6;
-// The five long-lived accumulators (derivatives of the site's three links, carries to two
-// links of the next layer) sit in per-thread LDS slots, 5 n_g reals per thread: 80 KB per
-// work-group for SU(3) in double precision, two work-groups per CU.  Held in registers
-// instead, SU(3) in double precision needs about 320 registers per lane (one wave per SIMD);
-// with the slots, 242 (two waves).
-#ifndef GL_MARCH_CACHE
-#define GL_MARCH_CACHE 1
-#endif
-#ifndef GL_MARCH_LDS_ACC
-#define GL_MARCH_LDS_ACC 1
-#endif
-#ifndef GL_MARCH_WAVES
-#define GL_MARCH_WAVES 2
-#endif
+// stages of a layer, and of the layer before a chunk (its carries)
+constexpr int MARCH_SUB = 4, MARCH_WARM = 2;
+// What lives across the stages sits in per-thread LDS slots: the derivatives of the site's x
+// and y links, which double as the carries to the next layer (2 n_g reals), and the site's z
+// links of both slices, loaded once per layer (2 stored links): 80 KB per work-group for
+// SU(3) in double precision, two work-groups per CU at two waves per SIMD.
+//
+// What bounds it: vector memory.  The columns that march at once hold about 30 MB per XCD
+// against 4 MB of L2, so a link that is loaded again in a later stage comes from beyond the L2.
+// So each stage forms every loop of a plane and loads each link it needs once: 32 links and
+// the field per site and layer, 3.5 KB, at 7 TB/s.  With one loop per micro-step (21 of them,
+// 55 links and 5 cached loops, 6.4 KB) an iteration at 512 x 64 x 64 FP64 took 1.51 ms,
+// now 1.06 ms, and the per-step force 1.53 ms, now 0.90 ms (means over a solve's launches).
+// Registers: a link is held as stored (24 registers instead of 36) and rebuilt at each use,
+// scheduling fences keep the products of a stage apart, projections are formed from the loops
+// where they are used, and loads take a uniform base and a 32-bit offset.  Without each of
+// these the kernel spilled 100-300 registers.
 
 // MarchIter (internal.h): Ebase = E(t - dt/2) + dt f1(U(t), U(t - dt)) (+ dt j on z links);
 // Et the iterate E(t + dt/2), updated in place; Ut_out the new trial links exp(i a dt E') U(t);
 // conv = [max |E' - E_old|, max |E'|] of this iteration (atomic max); F the MODE 0 output;
-// cache (3 planes of full matrices per site): the loops of slice A alone, C_xy, C_xz^{(A,A)}
-// and C_yz^{(A,A)} based at each site, which MODE 0 stores (it forms them anyway) and the
-// iterations of the step read back instead of forming them (A = U(t) is fixed for the step).
+// cache: the loops C_xy of slice A alone based at each site, special unitary and stored like
+// links, which MODE 0 stores (it forms them anyway) and the iterations of the step read back
+// (A = U(t) is fixed for the step).  The (x, z) and (y, z) loops of A alone are formed from
+// the links that their stage loads anyway.
 
 bool march_geometry(const Geom& g) { return g.nt >= 8 && g.nt <= 64 && 64 % g.nt == 0; }
-size_t march_cache_elems(const Geom& g, int nc) { return 3 * (size_t)(nc == 3 ? 18 : 4) * g.Vp; }
+size_t march_cache_elems(const Geom& g, int nc) { return (size_t)(nc == 3 ? SU3_STORED : 4) * g.Vp; }
 
 __device__ __forceinline__ void atomic_max_nn(double* addr, double v) {
   atomicMax((unsigned long long*)addr, (unsigned long long)__double_as_longlong(v));
 }
 
 template <typename G, typename T, int MODE>
-__global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(GL_MARCH_WAVES))) k_semi_march(const T* __restrict__ A, const T* __restrict__ B, Geom g,
-                                                         StepConst c, MarchIter it, int ncg, int nch, int lz) {
+__global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2))) k_semi_march(const T* __restrict__ A, const T* __restrict__ B, Geom g,
+                                                         MarchIter it, int ncg, int nch, int lz) {
   using L = typename G::Link;
   using Ag = typename G::Alg;
   using R = typename G::Real;
@@ -252,313 +192,426 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(G
   const int z0 = ch * lz;
   const int z1 = min(z0 + lz, g.nz);
   const XNbr xn = x_nbr(g, b0);
-  const R kxy = (R)(0.5 / (c.a[0] * c.a[0] * c.a[1] * c.a[1]));
-  const R kxz = (R)(0.25 / (c.a[0] * c.a[0] * c.a[2] * c.a[2]));
-  const R kyz = (R)(0.25 / (c.a[1] * c.a[1] * c.a[2] * c.a[2]));
-  const R h = R(0.5);
-  // Every load goes through an empty asm statement on its site index that also takes a
-  // token, a value of the last loop product formed: the compiler must treat it as a new
-  // load (reloading a link from the caches instead of keeping it, and forming a loop twice
-  // instead of keeping it, is what holds the register count down; merging identical loads
-  // would undo that), and cannot issue it before that product exists (hoisting the loads
-  // of all later loops to the top of the layer would hold their links live all along).
+  // Every load goes through an empty asm statement on its offset that also takes a token, a
+  // value of a loop product already formed: the compiler cannot merge it with an earlier load
+  // of the same link and cannot issue it before that product exists (hoisting the loads
+  // of later loops to the top of a stage would hold their links live all along).
   R tok = R(0);
-  // Links are addressed by byte offsets into a direction's record array: the layers are
-  // whole records (nt divides 64, nt >= 8), so the offset of a site is its layer's base
-  // plus an in-layer offset that only depends on (x, y), computed once per thread for the
-  // site and its +y and -y rows.
+  // Links are addressed by a uniform base (direction and layer) plus a 32-bit in-layer offset:
+  // the layers are whole records (nt divides 64, nt >= 8), so the offset only depends on
+  // (x, y) and is kept for the site and its +y and -y rows.
   constexpr int SW = StoredWidth<L>::value;
-  constexpr uint64_t RBYTES = RecShape<T, SW>::BYTES;
+  constexpr uint32_t RBYTES = RecShape<T, SW>::BYTES;
   const uint64_t dir_bytes = (uint64_t)Vp * SW * sizeof(T);
   const uint64_t layer_bytes = (uint64_t)(g.layer / 64) * RBYTES;
   auto in_layer = [&](int dy) __attribute__((always_inline)) {
     const uint32_t tt = (uint32_t)(wrap_add(b0.y, dy, g.nt) * g.nt + b0.x);
-    return (uint64_t)(tt / 64) * RBYTES + (uint64_t)(tt % 64) * 16;
+    return (tt / 64) * RBYTES + (tt % 64) * 16;
   };
-  const uint64_t o_t = in_layer(0), o_py = in_layer(1), o_my = in_layer(-1);
-  const int tmy = wrap_add(b0.y, -1, g.nt) * g.nt + b0.x;   // in-layer index of the -y neighbour
-  auto ld = [&](L& l, const T* U, int d, uint64_t off) __attribute__((always_inline)) {
+  const uint32_t o_t = in_layer(0), o_py = in_layer(1), o_my = in_layer(-1);
+  struct Raw {   // a link as stored (SU(3): two rows); full() rebuilds it at each use
+    R v[SW];
+  };
+  auto ld = [&](Raw& l, const T* U, int d, int z, uint32_t off) __attribute__((always_inline)) {
     asm volatile("" : "+v"(off) : "v"(tok));
     using NV = typename NVec16<T>::type;
-    const char* rec = (const char*)U + (uint64_t)d * dir_bytes + off;
-    R v[SW];
+    const char* base = (const char*)U + (uint64_t)d * dir_bytes + (uint64_t)z * layer_bytes;
 #pragma unroll
     for (int q = 0; q < SW * (int)sizeof(T) / 16; ++q) {
-      const NV x = *(const NV*)(rec + q * (RB * 16));
+      const NV x = *(const NV*)(base + q * (RB * 16) + off);
 #pragma unroll
-      for (int k = 0; k < 16 / (int)sizeof(T); ++k) v[q * (16 / (int)sizeof(T)) + k] = (R)x[k];
+      for (int k = 0; k < 16 / (int)sizeof(T); ++k) l.v[q * (16 / (int)sizeof(T)) + k] = (R)x[k];
     }
+  };
+  auto full = [&](Raw& r) __attribute__((always_inline)) -> L {
+#pragma unroll
+    for (int k = 0; k < SW / 2; ++k) asm volatile("" : "+v"(r.v[k]));   // no third row kept from an earlier use
+    L l;
+    link_from_stored(l, r.v);
+    return l;
+  };
+  auto pulled = [&](const Raw& r) __attribute__((always_inline)) -> L {   // of the lane at x + e_x
+    Raw p;
+#pragma unroll
+    for (int k = 0; k < SW; ++k) p.v[k] = lane_pull(r.v[k], xn.ap);
+    L l;
+    link_from_stored(l, p.v);
+    return l;
+  };
+  // the z links of the site on both slices, loaded once per layer into per-thread LDS slots of
+  // 16-byte chunks: zl(k) rebuilds slice k's (0 A, 1 B), zlx(k) that of the lane at x + e_x
+  using V16 = typename Vec16<T>::type;
+  constexpr int NCH = SW * (int)sizeof(T) / 16, VW = 16 / (int)sizeof(T);
+  __shared__ V16 zpark[2 * NCH * MARCH_BS];
+  auto park = [&](const Raw& r, int k) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NCH; ++q) {
+      V16 x;
+      T* e = (T*)&x;
+#pragma unroll
+      for (int j = 0; j < VW; ++j) e[j] = (T)r.v[q * VW + j];
+      zpark[(k * NCH + q) * MARCH_BS + threadIdx.x] = x;
+    }
+  };
+  auto unpark = [&](uint32_t slot, int k) __attribute__((always_inline)) -> L {
+    asm volatile("" : "+v"(slot));   // read again at each use
+    R v[SW];
+#pragma unroll
+    for (int q = 0; q < NCH; ++q) {
+      const V16 x = zpark[(k * NCH + q) * MARCH_BS + slot];
+      const T* e = (const T*)&x;
+#pragma unroll
+      for (int j = 0; j < VW; ++j) v[q * VW + j] = (R)e[j];
+    }
+    L l;
     link_from_stored(l, v);
+    return l;
   };
-  auto mark = [&](const L& m) __attribute__((always_inline)) { tok = link_token(m); };
-  // cached loop of slice A at site index si (MODE 1), or store of a formed one (MODE 0)
-  auto cached = [&](int plane, uint32_t si) __attribute__((always_inline)) -> L {
-    L m;
-    asm volatile("" : "+v"(si) : "v"(tok));
-    load_full(m, (const T*)it.cache, plane, si, Vp);
-    mark(m);
-    return m;
-  };
-  auto keep = [&](const L& m, int plane, uint32_t si, bool warm) __attribute__((always_inline)) {
-    if (GL_MARCH_CACHE && it.cache && !warm) store_full(m, (T*)it.cache, plane, si, Vp);
-  };
+  const uint32_t slot_x = (threadIdx.x & ~63u) + (uint32_t)(xn.ap >> 2);   // of the lane at x + e_x
+  auto zl = [&](int k) __attribute__((always_inline)) -> L { return unpark(threadIdx.x, k); };
+  auto zlx = [&](int k) __attribute__((always_inline)) -> L { return unpark(slot_x, k); };
+  auto fence = []() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
   double dmax = 0.0, emax = 0.0;
   bool bad = false;
-  // finish link d of site s with its complete derivative acc (dv/dX as components)
-  auto finish = [&](const Ag& acc, int d, uint32_t s, uint64_t own) __attribute__((always_inline)) {
-    const double ad = d == 0 ? c.a[0] : (d == 1 ? c.a[1] : c.a[2]);
-    Ag f;
-#pragma unroll
-    for (int k = 0; k < NG; ++k) f.c[k] = (R)(-ad) * acc.c[k];
+  // finish link d of site s with its complete derivative acc (dv/dX as components); u() = U_d(s)
+  // on slice A
+  auto finish = [&](const Ag& acc, int d, uint32_t s, auto&& u) __attribute__((always_inline)) {
     if constexpr (MODE == 0) {
+      Ag f;
+#pragma unroll
+      for (int k = 0; k < NG; ++k) f.c[k] = (R)it.ma[d] * acc.c[k];
       store_alg(f, (T*)it.F, d, s, Vp);
     } else {
       Ag e, eo;
       load_alg_own(e, (const T*)it.Ebase, d, s, Vp);
       load_alg_own(eo, (const T*)it.Et, d, s, Vp);
-      const R dt = (R)c.dt;
       const R om = (R)it.omega;
 #pragma unroll
       for (int k = 0; k < NG; ++k) {
-        const R en = fmx(dt, f.c[k], e.c[k]);
+        const R en = fmx((R)it.madt[d], acc.c[k], e.c[k]);
         dmax = fmax(dmax, fabs((double)en - (double)eo.c[k]));
         emax = fmax(emax, fabs((double)en));
         bad |= !isfinite((double)en);
         e.c[k] = fmx(om, en - eo.c[k], eo.c[k]);
       }
       store_alg(e, (T*)it.Et, d, s, Vp);
-      L u;
-      ld(u, A, d, own);
-      store_link(G::template expi_mul<true>(e, (R)(ad * c.dt), u), (T*)it.Ut_out, d, s, Vp);
+      const L w = G::expi(e, (R)-it.madt[d]);
+      fence();
+      store_link(G::mul(w, u()), (T*)it.Ut_out, d, s, Vp);
     }
   };
-  // the z link at s + e_i: from the next lane for i = x, from memory for i = y
-  auto zlink_i = [&](L& l, const T* U, int i, uint64_t s, uint64_t s_pi) __attribute__((always_inline)) {
-    ld(l, U, 2, i == 0 ? s : s_pi);
-    if (i == 0) l = pull_link(l, xn.ap);
-  };
-  // C^{(P,Q)}_{iz} based at s: transverse links of slice P, longitudinal of slice Q
-  auto loop_iz = [&](const T* P, const T* Q, int i, uint64_t s, uint64_t s_pi, uint64_t s_pz) __attribute__((always_inline)) -> L {
-    L a, bq;
-    ld(a, P, i, s);
-    zlink_i(bq, Q, i, s, s_pi);
-    L m = G::mul(a, bq);
-    ld(a, P, i, s_pz);
-    m = G::mul_dag(m, a);
-    ld(a, Q, 2, s);
-    m = G::mul_dag(m, a);
-    mark(m);
-    return m;
-  };
-  // P(C^{(P,Q)}_{iz}) without forming the last product
-  auto ploop_iz = [&](const T* P, const T* Q, int i, uint64_t s, uint64_t s_pi, uint64_t s_pz) __attribute__((always_inline)) -> Ag {
-    L a, bq;
-    ld(a, P, i, s);
-    zlink_i(bq, Q, i, s, s_pi);
-    L m = G::mul(a, bq);
-    ld(a, P, i, s_pz);
-    m = G::mul_dag(m, a);
-    ld(a, Q, 2, s);
-    const Ag r = G::proj_mul_dag(m, a);
-    tok = r.c[0];
-    return r;
-  };
-  // C_xy based at s on slice U (the y link at s + e_x from the next lane)
-  auto loop_xy = [&](const T* U, uint64_t s, uint64_t s_py) __attribute__((always_inline)) -> L {
-    L a, b;
-    ld(a, U, 0, s);
-    ld(b, U, 1, s);
-    L m = G::mul(a, pull_link(b, xn.ap));
-    ld(a, U, 0, s_py);
-    m = G::mul_dag(m, a);
-    m = G::mul_dag(m, b);
-    mark(m);
-    return m;
-  };
-  // P(C_xy) without forming the last product
-  auto ploop_xy = [&](const T* U, uint64_t s, uint64_t s_py) __attribute__((always_inline)) -> Ag {
-    L a, b;
-    ld(a, U, 0, s);
-    ld(b, U, 1, s);
-    L m = G::mul(a, pull_link(b, xn.ap));
-    ld(a, U, 0, s_py);
-    m = G::mul_dag(m, a);
-    const Ag r = G::proj_mul_dag(m, b);
-    tok = r.c[0];
-    return r;
-  };
-  // The work of a layer is a sequence of micro-steps, each forming one loop and handing its
-  // derivative on; each micro-step is its own basic block (a loop that is not unrolled over
-  // a switch on a uniform step number), so only the accumulators and at most two
-  // projections live across them and the instruction scheduler cannot interleave loops.
+  // The work of a layer is a sequence of four stages, each its own basic block (a loop that is
+  // not unrolled over a switch on a uniform stage number), so only the accumulators live across
+  // them.  A stage loads each link it needs once; the token orders the loads of its second half
+  // behind the loops of its first.
   //   fx, fy, fz: derivative of the site's x, y, z links; cx, cy: carries to the x, y links
-  //   of the next layer; P1, P2: projections held between the steps of one plane; snd: the
-  //   (x, z) loops' derivative for the z link at s + e_x, pulled by the next lane.
-  // Micro-steps 4-6 and 10-12 also serve the warm-up (the carries from the layer before the
-  // chunk), where their other outputs are discarded.
-#if GL_MARCH_LDS_ACC
-  __shared__ R acc_lds[5 * NG * MARCH_BS];
+  //   of the next layer; snd: the (x, z) loops' derivative for the z link at s + e_x, pulled by
+  //   the next lane.
+  // Stages 1 and 2 also serve the warm-up (the carries from the layer before the chunk),
+  // where their other outputs are discarded.
+  // fx doubles as the carry to the x link of the next layer (from the end of stage 1 on), fy as
+  // that to the y link: the derivative is complete when the next carry is
+  __shared__ R acc_lds[2 * NG * MARCH_BS];
   using A_ = AccL<MARCH_BS, Ag, R>;
-  A_ fx{acc_lds + 0 * NG * MARCH_BS + threadIdx.x}, fy{acc_lds + 1 * NG * MARCH_BS + threadIdx.x},
-      fz{acc_lds + 2 * NG * MARCH_BS + threadIdx.x}, cx{acc_lds + 3 * NG * MARCH_BS + threadIdx.x},
-      cy{acc_lds + 4 * NG * MARCH_BS + threadIdx.x};
-#else
-  using A_ = Acc<Ag, R, false>;
-  A_ fx, fy, fz, cx, cy;
-#endif
+  A_ fx{acc_lds + threadIdx.x}, fy{acc_lds + NG * MARCH_BS + threadIdx.x};
   fx.set(G::alg_zero());
   fy.set(G::alg_zero());
-  fz.set(G::alg_zero());
-  cx.set(G::alg_zero());
-  cy.set(G::alg_zero());
-  Ag P1 = G::alg_zero(), P2 = G::alg_zero(), snd = G::alg_zero();
+  Ag fz = G::alg_zero();
   constexpr int NSUB = MARCH_SUB, NWARM = MARCH_WARM;
   const int zm = z0 > 0 ? z0 - 1 : g.nz - 1;
   const int nq = NWARM + (z1 - z0) * NSUB;
 #pragma unroll 1
   for (int q = 0; q < nq; ++q) {
-    int z, sub;
-    if (q < NWARM) {
-      z = zm;
-      sub = q < 3 ? 4 + q : 7 + q;
-    } else {
-      z = z0 + (q - NWARM) / NSUB;
-      sub = (q - NWARM) % NSUB;
-    }
-    const int zp = z + 1 < g.nz ? z + 1 : 0;
-    // byte offsets of the site, its +y and -y neighbours, and the two at z + 1
-    const uint64_t lz = (uint64_t)z * layer_bytes, lzp = (uint64_t)zp * layer_bytes;
-    const uint64_t s = lz + o_t, s_py = lz + o_py, s_my = lz + o_my, s_pz = lzp + o_t, s_mypz = lzp + o_my;
-    const uint32_t site_z = (uint32_t)z * (uint32_t)g.layer + (uint32_t)t;   // site index (E, Et, outputs)
-    const uint32_t site_my = site_z - (uint32_t)t + (uint32_t)tmy;          // its -y neighbour
     const bool warm = q < NWARM;
-    L u;
-    switch (sub) {
-      // ---- (x, y) plane at the base: x link factor 0, y link factor 3, y link at s + e_x factor 1
-      case 0:
-        fx.set(cx.get());
-        fy.set(cy.get());
-        fz.set(G::alg_zero());
-        P1 = ploop_xy(B, s, s_py);
-        break;
-      case 1: {
-        const L CA = (MODE == 1 && GL_MARCH_CACHE) ? cached(0, site_z) : loop_xy(A, s, s_py);
-        if constexpr (MODE == 0) keep(CA, 0, site_z, warm);
-        const Ag hf = hs_herm<false>(CA, P1);
-        fx.add(h * kxy, hf);
-        fy.add(-h * kxy, hs_herm<true>(CA, P1));
-        ld(u, A, 0, s);
-        fy.add(h * kxy, pull_alg(G::transport(u, hf), xn.am));
-        break;
-      }
-      // ---- (x, y) plane at base - e_y: the x link is its factor 2 (daggered), W = C F3
-      case 2:
-        P1 = ploop_xy(B, s_my, s);
-        break;
-      case 3: {
-        const L CA = (MODE == 1 && GL_MARCH_CACHE) ? cached(0, site_my) : loop_xy(A, s_my, s);
-        ld(u, A, 1, s_my);
-        fx.add(-h * kxy, G::transport(u, hs_herm<true>(CA, P1)));
+    const int z = warm ? zm : z0 + (q - NWARM) / NSUB;
+    const int stage = warm ? 1 + q : (q - NWARM) % NSUB;
+    const int zp = z + 1 < g.nz ? z + 1 : 0;
+    const uint32_t site_z = (uint32_t)z * (uint32_t)g.layer + (uint32_t)t;   // site index (E, Et, outputs)
+    switch (stage) {
+      // ---- (x, y) plane at the base: x link factor 0, y link factor 3, y link at s + e_x factor
+      // 1; then at base - e_y, where the x link is factor 2 (daggered), W = C F3
+      case 0: {
+        Raw u, v, w;
+        L m;
+        ld(u, B, 0, z, o_t);
+        ld(v, B, 1, z, o_t);
+        ld(w, B, 0, z, o_py);
+        m = G::mul(full(u), pulled(v));
+        fence();
+        m = G::mul_dag(m, full(w));
+        fence();
+        Ag P = G::proj_mul_dag(m, full(v));
+        tok = P.c[0];
+        fence();
+        // the loop of slice A alone: MODE 0 forms and stores it, MODE 1 reads it back
+        if constexpr (MODE == 0) {
+          Raw x;
+          ld(x, A, 0, z, o_t);
+          ld(v, A, 1, z, o_t);
+          ld(w, A, 0, z, o_py);
+          m = G::mul(full(x), pulled(v));
+          fence();
+          m = G::mul_dag(m, full(w));
+          fence();
+          m = G::mul_dag(m, full(v));
+          store_link(m, (T*)it.cache, 0, site_z, Vp);
+          v = x;
+        } else {
+          ld(w, (const T*)it.cache, 0, z, o_t);
+          ld(v, A, 0, z, o_t);
+          m = full(w);
+        }
+        fence();
+        Ag fv = fx.get();   // the carry
+        const Ag hf = hs_herm<false>(m, P);
+        axpy(fv, (R)it.k[0], hf);
+        Ag gv = fy.get();
+        axpy(gv, (R)-it.k[0], hs_herm<true>(m, P));
+        fence();
+        axpy(gv, (R)it.k[0], pull_alg(G::transport(full(v), hf), xn.am));
+        fy.set(gv);
+        tok = gv.c[0];
+        fence();
+        ld(w, B, 0, z, o_my);
+        ld(v, B, 1, z, o_my);
+        m = G::mul(full(w), pulled(v));
+        fence();
+        m = G::mul_dag(m, full(u));
+        fence();
+        P = G::proj_mul_dag(m, full(v));
+        tok = P.c[0];
+        fence();
+        if constexpr (MODE == 0) {
+          ld(u, A, 0, z, o_my);
+          ld(v, A, 1, z, o_my);
+          ld(w, A, 0, z, o_t);
+          m = G::mul(full(u), pulled(v));
+          fence();
+          m = G::mul_dag(m, full(w));
+          fence();
+          m = G::mul_dag(m, full(v));
+        } else {
+          ld(w, (const T*)it.cache, 0, z, o_my);
+          ld(v, A, 1, z, o_my);
+          m = full(w);
+        }
+        fence();
+        const Ag hb = hs_herm<true>(m, P);
+        fence();
+        axpy(fv, (R)-it.k[0], G::transport(full(v), hb));
+        fx.set(fv);
+        tok = fv.c[0];
         break;
       }
       // ---- (x, z) plane at the base: x link factor 0, z link factor 3, x link at s + e_z
       // factor 2 (carry), z link at s + e_x factor 1 (snd)
-      case 4:
-        P1 = ploop_iz(A, B, 0, s, s, s_pz);
-        break;
-      case 5: {
-        const L Caa = (MODE == 1 && GL_MARCH_CACHE) ? cached(1, site_z) : loop_iz(A, A, 0, s, s, s_pz);
-        if constexpr (MODE == 0) keep(Caa, 1, site_z, warm);
-        P2 = G::proj(Caa);
-        const Ag h1 = hs_herm<false>(Caa, P1);
-        const Ag hb1 = hs_herm<true>(Caa, P1);
-        fx.add(h * kxz, h1);
-        fz.add(-h * kxz, hb1);
-        ld(u, A, 2, s);
-        cx.set(G::transport(u, hb1));
-        ld(u, A, 0, s);
-        snd = G::transport(u, h1);
+      case 1: {
+        Raw a0, u;
+        L ca, cb;
+        {
+          Raw b2, a2;
+          ld(b2, B, 2, z, o_t);
+          ld(a2, A, 2, z, o_t);
+          ld(a0, A, 0, z, o_t);
+          ld(u, A, 0, zp, o_t);
+          park(a2, 0);
+          park(b2, 1);
+        }
+        // the wavefront's own writes before its other lanes' reads
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        cb = G::mul(full(a0), zlx(1));
+        fence();
+        cb = G::mul_dag(cb, full(u));
+        fence();
+        cb = G::mul_dag(cb, zl(1));
+        fence();
+        ca = G::mul(full(a0), zlx(0));
+        fence();
+        ca = G::mul_dag(ca, full(u));
+        fence();
+        ca = G::mul_dag(ca, zl(0));
+        fence();
+        if (!warm) {
+          Ag hf = hs_herm<false>(ca, G::proj(cb));
+          fx.add((R)it.k[1], hf);
+          fence();
+          hf = G::transport(full(a0), hf);   // on the z link at s + e_x
+          fence();
+          fz = pull_alg(hf, xn.am);
+          hf = hs_herm<false>(cb, G::proj(ca));
+          fx.add((R)it.k[1], hf);
+          fence();
+        }
+        Ag cv = hs_herm<true>(ca, G::proj(cb));
+        axpy(fz, R(-1), cv);
+        fence();
+        cv = G::transport(zl(0), cv);
+        fence();
+        {
+          const Ag hb = hs_herm<true>(cb, G::proj(ca));
+          fence();
+          axpy(cv, R(1), G::transport(zl(1), hb));
+        }
+        fence();
+#pragma unroll
+        for (int k = 0; k < NG; ++k) cv.c[k] *= (R)-it.k[1];
+        const Ag fv = fx.get();
+        fx.set(cv);   // from here on the carry to the next layer
+        tok = cv.c[0];
+        if (warm) break;
+        finish(fv, 0, site_z, [&]() { return full(a0); });   // the x link is complete
+        fence();
+        ld(u, B, 0, z, o_t);
+        ld(a0, B, 0, zp, o_t);
+        cb = G::mul(full(u), zlx(1));
+        fence();
+        cb = G::mul_dag(cb, full(a0));
+        fence();
+        const Ag P = G::proj_mul_dag(cb, zl(1));
+        fence();
+        ca = G::mul(full(u), zlx(0));
+        fence();
+        ca = G::mul_dag(ca, full(a0));
+        fence();
+        ca = G::mul_dag(ca, zl(0));
+        fence();
+        axpy(fz, R(-1), hs_herm<true>(ca, P));
+        fence();
+        {
+          const Ag hf = hs_herm<false>(ca, P);
+          fence();
+          axpy(fz, R(1), pull_alg(G::transport(full(u), hf), xn.am));
+        }
+#pragma unroll
+        for (int k = 0; k < NG; ++k) fz.c[k] *= (R)it.k[1];
+        tok = fz.c[0];
         break;
       }
-      case 6: {
-        const L Cab = loop_iz(A, B, 0, s, s, s_pz);
-        fx.add(h * kxz, hs_herm<false>(Cab, P2));
-        ld(u, B, 2, s);
-        cx.add(R(1), G::transport(u, hs_herm<true>(Cab, P2)));
-        cx.scale(-h * kxz);
-        break;
-      }
-      case 7:
-        P1 = ploop_iz(B, B, 0, s, s, s_pz);
-        break;
-      case 8: {
-        const L Cba = loop_iz(B, A, 0, s, s, s_pz);
-        fz.add(-h * kxz, hs_herm<true>(Cba, P1));
-        ld(u, B, 0, s);
-        axpy(snd, R(1), G::transport(u, hs_herm<false>(Cba, P1)));
-        fz.add(h * kxz, pull_alg(snd, xn.am));
-        break;
-      }
-      case 9:
-        finish(fx.get(), 0, site_z, s);   // the x link is complete
-        break;
       // ---- (y, z) plane at the base: y link factor 0, z link factor 3, y link at s + e_z
       // factor 2 (carry); its factor 1 (z link at s + e_y) is formed by the site above
-      case 10:
-        P1 = ploop_iz(A, B, 1, s, s_py, s_pz);
-        break;
-      case 11: {
-        const L Caa = (MODE == 1 && GL_MARCH_CACHE) ? cached(2, site_z) : loop_iz(A, A, 1, s, s_py, s_pz);
-        if constexpr (MODE == 0) keep(Caa, 2, site_z, warm);
-        P2 = G::proj(Caa);
-        const Ag hb1 = hs_herm<true>(Caa, P1);
-        fy.add(h * kyz, hs_herm<false>(Caa, P1));
-        fz.add(-h * kyz, hb1);
-        ld(u, A, 2, s);
-        cy.set(G::transport(u, hb1));
+      case 2: {
+        Raw a1, u, v;
+        L ca, cb;
+        ld(a1, A, 1, z, o_t);
+        ld(v, B, 2, z, o_py);
+        ld(u, A, 1, zp, o_t);
+        cb = G::mul(full(a1), full(v));
+        tok = link_token(cb);
+        fence();
+        ld(v, A, 2, z, o_py);
+        cb = G::mul_dag(cb, full(u));
+        fence();
+        cb = G::mul_dag(cb, zl(1));
+        fence();
+        ca = G::mul(full(a1), full(v));
+        fence();
+        ca = G::mul_dag(ca, full(u));
+        fence();
+        ca = G::mul_dag(ca, zl(0));
+        fence();
+        if (!warm) {
+          fy.add((R)it.k[2], hs_herm<false>(ca, G::proj(cb)));
+          fence();
+          fy.add((R)it.k[2], hs_herm<false>(cb, G::proj(ca)));
+          fence();
+        }
+        Ag cv = hs_herm<true>(ca, G::proj(cb));
+        axpy(fz, (R)-it.k[2], cv);
+        fence();
+        cv = G::transport(zl(0), cv);
+        fence();
+        {
+          const Ag hb = hs_herm<true>(cb, G::proj(ca));
+          fence();
+          axpy(cv, R(1), G::transport(zl(1), hb));
+        }
+        fence();
+#pragma unroll
+        for (int k = 0; k < NG; ++k) cv.c[k] *= (R)-it.k[2];
+        const Ag fv = fy.get();
+        fy.set(cv);   // from here on the carry to the next layer
+        tok = cv.c[0];
+        if (warm) break;
+        finish(fv, 1, site_z, [&]() { return full(a1); });   // the y link is complete
+        fence();
+        ld(u, B, 1, z, o_t);
+        ld(a1, B, 1, zp, o_t);
+        {
+          Raw w;
+          ld(w, B, 2, z, o_py);
+          cb = G::mul(full(u), full(w));
+        }
+        fence();
+        cb = G::mul_dag(cb, full(a1));
+        fence();
+        const Ag P = G::proj_mul_dag(cb, zl(1));
+        fence();
+        ca = G::mul(full(u), full(v));
+        fence();
+        ca = G::mul_dag(ca, full(a1));
+        fence();
+        ca = G::mul_dag(ca, zl(0));
+        fence();
+        const Ag hb = hs_herm<true>(ca, P);
+        axpy(fz, (R)-it.k[2], hb);
+        tok = hb.c[0];
         break;
       }
-      case 12: {
-        const L Cab = loop_iz(A, B, 1, s, s_py, s_pz);
-        fy.add(h * kyz, hs_herm<false>(Cab, P2));
-        ld(u, B, 2, s);
-        cy.add(R(1), G::transport(u, hs_herm<true>(Cab, P2)));
-        cy.scale(-h * kyz);
-        break;
-      }
-      case 13:
-        P1 = ploop_iz(B, B, 1, s, s_py, s_pz);
-        break;
-      case 14: {
-        const L Cba = loop_iz(B, A, 1, s, s_py, s_pz);
-        fz.add(-h * kyz, hs_herm<true>(Cba, P1));
-        break;
-      }
-      case 15:
-        finish(fy.get(), 1, site_z, s);   // the y link is complete
-        break;
       // ---- (y, z) plane at base - e_y: the z link is its factor 1, W = F0 (the y link at s - e_y)
-      case 16:
-        P1 = ploop_iz(A, B, 1, s_my, s, s_mypz);
-        break;
-      case 17: {
-        const L Caa = (MODE == 1 && GL_MARCH_CACHE) ? cached(2, site_my) : loop_iz(A, A, 1, s_my, s, s_mypz);
-        ld(u, A, 1, s_my);
-        fz.add(h * kyz, G::transport(u, hs_herm<false>(Caa, P1)));
+      default: {
+        Raw f0, f2, v, w;
+        L m;
+        ld(f0, A, 1, z, o_my);
+        ld(f2, A, 1, zp, o_my);
+        ld(w, B, 2, z, o_my);
+        m = G::mul(full(f0), zl(1));
+        fence();
+        m = G::mul_dag(m, full(f2));
+        tok = link_token(m);
+        fence();
+        ld(v, A, 2, z, o_my);
+        Ag P = G::proj_mul_dag(m, full(w));
+        fence();
+        m = G::mul(full(f0), zl(0));
+        fence();
+        m = G::mul_dag(m, full(f2));
+        fence();
+        m = G::mul_dag(m, full(v));
+        tok = link_token(m);
+        fence();
+        Raw g0;
+        ld(g0, B, 1, z, o_my);
+        ld(f2, B, 1, zp, o_my);
+        {
+          const Ag hf = hs_herm<false>(m, P);
+          fence();
+          axpy(fz, (R)it.k[2], G::transport(full(f0), hf));
+        }
+        fence();
+        m = G::mul(full(g0), zl(1));
+        fence();
+        m = G::mul_dag(m, full(f2));
+        fence();
+        P = G::proj_mul_dag(m, full(w));
+        fence();
+        m = G::mul(full(g0), zl(0));
+        fence();
+        m = G::mul_dag(m, full(f2));
+        fence();
+        m = G::mul_dag(m, full(v));
+        fence();
+        {
+          const Ag hf = hs_herm<false>(m, P);
+          fence();
+          axpy(fz, (R)it.k[2], G::transport(full(g0), hf));
+        }
+        tok = fz.c[0];
+        fence();
+        finish(fz, 2, site_z, [&]() { return zl(0); });   // the z link is complete
         break;
       }
-      case 18:
-        P1 = ploop_iz(B, B, 1, s_my, s, s_mypz);
-        break;
-      case 19: {
-        const L Cba = loop_iz(B, A, 1, s_my, s, s_mypz);
-        ld(u, B, 1, s_my);
-        fz.add(h * kyz, G::transport(u, hs_herm<false>(Cba, P1)));
-        break;
-      }
-      default:
-        finish(fz.get(), 2, site_z, s);   // the z link is complete
-        break;
     }
   }
   if constexpr (MODE == 1) {
@@ -575,13 +628,13 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(G
 }
 
 // Layers per chunk of the march.  A chunk first repeats the loops of the layer before it that
-// feed its carries (MARCH_WARM of the MARCH_SUB micro-steps of a layer), and a wavefront does
-// its micro-steps one after the other, so a launch takes (MARCH_WARM + lz MARCH_SUB) micro-steps
+// feed its carries (MARCH_WARM of the MARCH_SUB stages of a layer), and a wavefront does
+// its stages one after the other, so a launch takes (MARCH_WARM + lz MARCH_SUB) stages
 // for every round of work-groups that the chip holds at once.  The length with the fewest is
 // taken (the longest of equals: less repeated work): 16 layers on 512 x 64 x 64, which fill
 // the chip in one round (8 layers, two rounds: 7% slower), down to single layers where the
 // lattice is too small to fill it: 96 x 32 x 32 FP64, 24 work-groups of 16 layers 0.595 ms per
-// iteration, 384 of one layer 0.109 ms.  The result does not depend on the length
+// iteration, 384 of one layer 0.109 ms (0.089 ms with four stages per layer).  The result does not depend on the length
 // (the repeated loops are the same operations on the same links).
 constexpr int MARCH_LZ_MAX = 16;
 inline int march_chunk(int ncg, int nz, int resident) {
@@ -596,18 +649,28 @@ inline int march_chunk(int ncg, int nz, int resident) {
 }
 
 template <typename G, typename T>
-void launch_semi_march(const T* A, const T* B, const Geom& g, const StepConst& c, int mode, const MarchIter& it,
+void launch_semi_march(const T* A, const T* B, const Geom& g, const StepConst& c, int mode, const MarchIter& it_,
                        hipStream_t st) {
   const int ncol = (int)(g.layer / 64);
   const int ncg = (ncol + MARCH_BS / 64 - 1) / (MARCH_BS / 64);
-  // work-groups resident at once: two per CU at the kernel's two waves per SIMD, 256 CUs
-  const int lz = march_chunk(ncg, g.nz, 2 * 256);
+  MarchIter it = it_;
+  it.k[0] = 0.25 / (c.a[0] * c.a[0] * c.a[1] * c.a[1]);
+  it.k[1] = 0.125 / (c.a[0] * c.a[0] * c.a[2] * c.a[2]);
+  it.k[2] = 0.125 / (c.a[1] * c.a[1] * c.a[2] * c.a[2]);
+  for (int d = 0; d < 3; ++d) {
+    it.ma[d] = -c.a[d];
+    it.madt[d] = -c.a[d] * c.dt;
+  }
+  // work-groups resident at once on 256 CUs, from the kernel's registers: 2 per CU for SU(3) in
+  // double precision, 3 for SU(3) in single and SU(2) in double, 5 for SU(2) in single precision
+  constexpr int per_cu = sizeof(T) == 8 ? (G::NC == 3 ? 2 : 3) : (G::NC == 3 ? 3 : 5);
+  const int lz = march_chunk(ncg, g.nz, per_cu * 256);
   const int nch = (g.nz + lz - 1) / lz;
   const dim3 grid((unsigned)(ncg * nch));
   if (mode == 0)
-    hipLaunchKernelGGL((k_semi_march<G, T, 0>), grid, dim3(MARCH_BS), 0, st, A, B, g, c, it, ncg, nch, lz);
+    hipLaunchKernelGGL((k_semi_march<G, T, 0>), grid, dim3(MARCH_BS), 0, st, A, B, g, it, ncg, nch, lz);
   else
-    hipLaunchKernelGGL((k_semi_march<G, T, 1>), grid, dim3(MARCH_BS), 0, st, A, B, g, c, it, ncg, nch, lz);
+    hipLaunchKernelGGL((k_semi_march<G, T, 1>), grid, dim3(MARCH_BS), 0, st, A, B, g, it, ncg, nch, lz);
 }
 
 #define GL_MARCH_INST(G, T) \

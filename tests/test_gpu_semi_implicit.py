@@ -314,8 +314,8 @@ def test_full_size_semi_implicit_sampled(hop):
 @pytest.mark.parametrize("nc,nt,nz,reps", [(3, 8, 10, 103), (2, 8, 10, 800), (2, 64, 3, 30)])
 def test_march_chunk_lengths_agree(nc, nt, nz, reps):
     """The marching pass cuts the layers into chunks whose length follows from the lattice's
-    size: nz layers of a state that repeats `reps` times along z (chunks of 3 layers, the
-    last one short; of 16; of 3 over several column groups) against the nz layers alone
+    size: nz layers of a state that repeats `reps` times along z (chunks of several layers,
+    the last one short; many of them; several column groups) against the nz layers alone
     (chunks of 1).  Same operations on the same links: bitwise equal, through hops."""
     pkg = lattice_or_skip()
     w = synth.Workload(f"su{nc}-{nz}x{nt}", nc=nc, nz=nz, nt=nt, dt=1.0, mu=0.5, sigma=1.5, seed=390 + nt)
