@@ -119,7 +119,7 @@ template <typename G, typename T>
 void launch_semi_iter(const T* Uc, const T* Ut_in, const T* Ebase, T* Et, T* Ut_out, double* conv,
                       const double* conv_prev, double tol, const Geom& g, const StepConst& c, hipStream_t st,
                       const T* cache);
-// The marching pass (semi_march.hip) for lattices with 8 <= nt <= 64, nt dividing 64:
+// The marching pass (semi_march.hip) for lattices with 8 <= nt <= 64:
 // mode 0 writes f1(A, B) to it.F; mode 1 is one fixed-point iteration (A = U(t), B = the
 // trial links) with the fields of it.
 struct MarchIter {

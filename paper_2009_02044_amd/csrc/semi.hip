@@ -299,7 +299,7 @@ __device__ __forceinline__ bool semi_converged(const double* conv, double tol) {
 // (+inf if E' is not finite), conv[1] = max |E'| (component-wise).  When the previous
 // iteration's slot conv_prev already passes the test the iteration does nothing (every
 // thread returns): the host enqueues several iterations at once and reads their slots
-// afterwards.  (Lattices whose rows fill wavefronts use the marching pass of semi_march.hip.)
+// afterwards.  (Lattices with rows of 8 to 64 sites use the marching pass of semi_march.hip.)
 template <typename G, typename T, int d>
 __device__ __forceinline__ void semi_iter_body(const T* __restrict__ Uc, const T* __restrict__ Ut_in,
                                                const T* __restrict__ Ebase, T* __restrict__ Et,

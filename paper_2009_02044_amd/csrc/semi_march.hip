@@ -1,9 +1,9 @@
 // Semi-implicit scheme: the slice force f1(A, B) of every link in one pass (Sec. 3, fig. wilson;
 // the potential between two time slices and the derivative rule are stated in semi.hip).
 //
-// A wavefront owns a column of 64 consecutive sites of a layer (nt divides 64 and
-// nt >= 8: whole x rows, x neighbours in adjacent lanes) and marches along z through
-// a chunk of layers.  At each layer it forms the plaquette-like loops based at its sites
+// A wavefront owns a column of whole x rows of a layer (8 <= nt <= 64: 64 / nt of them, x
+// neighbours in other lanes) and marches along z through a
+// chunk of layers.  At each layer it forms the plaquette-like loops based at its sites
 // once and hands each loop's derivative to the links that carry it:
 //   * links of its own site: accumulated directly;
 //   * links at x + e_x (factor 1 of an (x, y) or (x, z) loop): pulled by the next lane;
@@ -155,14 +155,19 @@ constexpr int MARCH_SUB = 4, MARCH_WARM = 2;
 // (A = U(t) is fixed for the step).  The (x, z) and (y, z) loops of A alone are formed from
 // the links that their stage loads anyway.
 
-bool march_geometry(const Geom& g) { return g.nt >= 8 && g.nt <= 64 && 64 % g.nt == 0; }
+// Rows of 8 to 64 sites.  A row that leaves lanes idle (33: 31 of 64) still pays: two steps of 2.1 million
+// sites at dt = a_L took 83-89 ms with a kernel per link direction (semi.hip) and take 59 ms at nt =
+// 33, 47-50 ms at 45 and 48, 42 ms at 28 (38 ms at 64).
+bool march_geometry(const Geom& g) { return g.nt >= 8 && g.nt <= 64; }
 size_t march_cache_elems(const Geom& g, int nc) { return (size_t)(nc == 3 ? SU3_STORED : 4) * g.Vp; }
 
 __device__ __forceinline__ void atomic_max_nn(double* addr, double v) {
   atomicMax((unsigned long long*)addr, (unsigned long long)__double_as_longlong(v));
 }
 
-template <typename G, typename T, int MODE>
+// AL: layers are whole records (nt^2 a multiple of 64), so an offset only depends on (x, y) and is
+// formed once; with the general form everywhere 512 x 64 x 64 took 2.7% longer.
+template <typename G, typename T, int MODE, bool AL>
 __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2))) k_semi_march(const T* __restrict__ A, const T* __restrict__ B, Geom g,
                                                          MarchIter it, int ncg, int nch, int lz) {
   using L = typename G::Link;
@@ -182,40 +187,55 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
   const uint32_t bid = xcd_remap(blockIdx.x, nb);
   const int cg = (int)(bid % (uint32_t)ncg), ch = (int)(bid / (uint32_t)ncg);
   const int col = cg * (MARCH_BS / 64) + (int)(threadIdx.x >> 6);
-  const int ncol = (int)(g.layer / 64);
-  if (col >= ncol || ch >= nch) return;   // uniform over the wavefront
+  const int rpw = 64 / g.nt;   // rows per wavefront
+  if (col * rpw >= g.nt || ch >= nch) return;   // uniform over the wavefront
   const int lane = (int)(threadIdx.x & 63u);
-  const int t = col * 64 + lane;
+  // a lane without a site of its own does the first lane's work (the same loads, pulls and
+  // stores of the same values): no store is masked, which would split the stages' blocks
+  const int as = lane < rpw * g.nt && col * rpw + lane / g.nt < g.nt ? lane : 0;
   Site b0;
-  b0.x = t % g.nt;
-  b0.y = t / g.nt;
+  b0.x = as % g.nt;
+  b0.y = col * rpw + as / g.nt;
   const int z0 = ch * lz;
   const int z1 = min(z0 + lz, g.nz);
-  const XNbr xn = x_nbr(g, b0);
+  XNbr xn;
+  xn.ap = 4 * (as + (b0.x + 1 < g.nt ? 1 : 1 - g.nt));
+  xn.am = 4 * (as + (b0.x > 0 ? -1 : g.nt - 1));
   // Every load goes through an empty asm statement on its offset that also takes a token, a
   // value of a loop product already formed: the compiler cannot merge it with an earlier load
   // of the same link and cannot issue it before that product exists (hoisting the loads
   // of later loops to the top of a stage would hold their links live all along).
   R tok = R(0);
-  // Links are addressed by a uniform base (direction and layer) plus a 32-bit in-layer offset:
-  // the layers are whole records (nt divides 64, nt >= 8), so the offset only depends on
-  // (x, y) and is kept for the site and its +y and -y rows.
+  // Links are addressed by a uniform base (direction, and the record in which the layer starts)
+  // plus a 32-bit offset from there.
   constexpr int SW = StoredWidth<L>::value;
   constexpr uint32_t RBYTES = RecShape<T, SW>::BYTES;
   const uint64_t dir_bytes = (uint64_t)Vp * SW * sizeof(T);
-  const uint64_t layer_bytes = (uint64_t)(g.layer / 64) * RBYTES;
-  auto in_layer = [&](int dy) __attribute__((always_inline)) {
-    const uint32_t tt = (uint32_t)(wrap_add(b0.y, dy, g.nt) * g.nt + b0.x);
-    return (tt / 64) * RBYTES + (tt % 64) * 16;
+  // offset of in-layer index q where the layer's first site is site ph of its record
+  auto in_layer = [](uint32_t q, uint32_t ph) __attribute__((always_inline)) {
+    return ((q + ph) / RB) * RBYTES + ((q + ph) % RB) * 16;
   };
-  const uint32_t o_t = in_layer(0), o_py = in_layer(1), o_my = in_layer(-1);
+  // the site and its +y and -y neighbours in the layer: index, or (AL) offset
+  const uint32_t t = (uint32_t)(b0.y * g.nt + b0.x);
+  auto place = [&](uint32_t q) __attribute__((always_inline)) { return AL ? in_layer(q, 0) : q; };
+  const uint32_t o_t = place(t), o_py = place((uint32_t)(wrap_add(b0.y, 1, g.nt) * g.nt + b0.x)),
+                 o_my = place((uint32_t)(wrap_add(b0.y, -1, g.nt) * g.nt + b0.x));
+  struct Layer {   // its first record's offset in a direction, and its first site's place there
+    uint64_t rec;
+    uint32_t ph;
+  };
+  auto layer_at = [&](int z) __attribute__((always_inline)) {
+    const uint32_t s0 = (uint32_t)z * (uint32_t)g.layer;
+    return Layer{(uint64_t)(s0 / RB) * RBYTES, AL ? 0u : s0 % RB};
+  };
   struct Raw {   // a link as stored (SU(3): two rows); full() rebuilds it at each use
     R v[SW];
   };
-  auto ld = [&](Raw& l, const T* U, int d, int z, uint32_t off) __attribute__((always_inline)) {
+  auto ld = [&](Raw& l, const T* U, int d, const Layer& y, uint32_t q) __attribute__((always_inline)) {
+    uint32_t off = AL ? q : in_layer(q, y.ph);
     asm volatile("" : "+v"(off) : "v"(tok));
     using NV = typename NVec16<T>::type;
-    const char* base = (const char*)U + (uint64_t)d * dir_bytes + (uint64_t)z * layer_bytes;
+    const char* base = (const char*)U + (uint64_t)d * dir_bytes + y.rec;
 #pragma unroll
     for (int q = 0; q < SW * (int)sizeof(T) / 16; ++q) {
       const NV x = *(const NV*)(base + q * (RB * 16) + off);
@@ -326,16 +346,17 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
     const int z = warm ? zm : z0 + (q - NWARM) / NSUB;
     const int stage = warm ? 1 + q : (q - NWARM) % NSUB;
     const int zp = z + 1 < g.nz ? z + 1 : 0;
-    const uint32_t site_z = (uint32_t)z * (uint32_t)g.layer + (uint32_t)t;   // site index (E, Et, outputs)
+    const Layer ly = layer_at(z), lyp = layer_at(zp);
+    const uint32_t site_z = (uint32_t)z * (uint32_t)g.layer + t;   // site index (E, Et, outputs)
     switch (stage) {
       // ---- (x, y) plane at the base: x link factor 0, y link factor 3, y link at s + e_x factor
       // 1; then at base - e_y, where the x link is factor 2 (daggered), W = C F3
       case 0: {
         Raw u, v, w;
         L m;
-        ld(u, B, 0, z, o_t);
-        ld(v, B, 1, z, o_t);
-        ld(w, B, 0, z, o_py);
+        ld(u, B, 0, ly, o_t);
+        ld(v, B, 1, ly, o_t);
+        ld(w, B, 0, ly, o_py);
         m = G::mul(full(u), pulled(v));
         fence();
         m = G::mul_dag(m, full(w));
@@ -346,9 +367,9 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         // the loop of slice A alone: MODE 0 forms and stores it, MODE 1 reads it back
         if constexpr (MODE == 0) {
           Raw x;
-          ld(x, A, 0, z, o_t);
-          ld(v, A, 1, z, o_t);
-          ld(w, A, 0, z, o_py);
+          ld(x, A, 0, ly, o_t);
+          ld(v, A, 1, ly, o_t);
+          ld(w, A, 0, ly, o_py);
           m = G::mul(full(x), pulled(v));
           fence();
           m = G::mul_dag(m, full(w));
@@ -357,8 +378,8 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
           store_link(m, (T*)it.cache, 0, site_z, Vp);
           v = x;
         } else {
-          ld(w, (const T*)it.cache, 0, z, o_t);
-          ld(v, A, 0, z, o_t);
+          ld(w, (const T*)it.cache, 0, ly, o_t);
+          ld(v, A, 0, ly, o_t);
           m = full(w);
         }
         fence();
@@ -372,8 +393,8 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         fy.set(gv);
         tok = gv.c[0];
         fence();
-        ld(w, B, 0, z, o_my);
-        ld(v, B, 1, z, o_my);
+        ld(w, B, 0, ly, o_my);
+        ld(v, B, 1, ly, o_my);
         m = G::mul(full(w), pulled(v));
         fence();
         m = G::mul_dag(m, full(u));
@@ -382,17 +403,17 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         tok = P.c[0];
         fence();
         if constexpr (MODE == 0) {
-          ld(u, A, 0, z, o_my);
-          ld(v, A, 1, z, o_my);
-          ld(w, A, 0, z, o_t);
+          ld(u, A, 0, ly, o_my);
+          ld(v, A, 1, ly, o_my);
+          ld(w, A, 0, ly, o_t);
           m = G::mul(full(u), pulled(v));
           fence();
           m = G::mul_dag(m, full(w));
           fence();
           m = G::mul_dag(m, full(v));
         } else {
-          ld(w, (const T*)it.cache, 0, z, o_my);
-          ld(v, A, 1, z, o_my);
+          ld(w, (const T*)it.cache, 0, ly, o_my);
+          ld(v, A, 1, ly, o_my);
           m = full(w);
         }
         fence();
@@ -410,10 +431,10 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         L ca, cb;
         {
           Raw b2, a2;
-          ld(b2, B, 2, z, o_t);
-          ld(a2, A, 2, z, o_t);
-          ld(a0, A, 0, z, o_t);
-          ld(u, A, 0, zp, o_t);
+          ld(b2, B, 2, ly, o_t);
+          ld(a2, A, 2, ly, o_t);
+          ld(a0, A, 0, ly, o_t);
+          ld(u, A, 0, lyp, o_t);
           park(a2, 0);
           park(b2, 1);
         }
@@ -463,8 +484,8 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         if (warm) break;
         finish(fv, 0, site_z, [&]() { return full(a0); });   // the x link is complete
         fence();
-        ld(u, B, 0, z, o_t);
-        ld(a0, B, 0, zp, o_t);
+        ld(u, B, 0, ly, o_t);
+        ld(a0, B, 0, lyp, o_t);
         cb = G::mul(full(u), zlx(1));
         fence();
         cb = G::mul_dag(cb, full(a0));
@@ -494,13 +515,13 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
       case 2: {
         Raw a1, u, v;
         L ca, cb;
-        ld(a1, A, 1, z, o_t);
-        ld(v, B, 2, z, o_py);
-        ld(u, A, 1, zp, o_t);
+        ld(a1, A, 1, ly, o_t);
+        ld(v, B, 2, ly, o_py);
+        ld(u, A, 1, lyp, o_t);
         cb = G::mul(full(a1), full(v));
         tok = link_token(cb);
         fence();
-        ld(v, A, 2, z, o_py);
+        ld(v, A, 2, ly, o_py);
         cb = G::mul_dag(cb, full(u));
         fence();
         cb = G::mul_dag(cb, zl(1));
@@ -536,11 +557,11 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         if (warm) break;
         finish(fv, 1, site_z, [&]() { return full(a1); });   // the y link is complete
         fence();
-        ld(u, B, 1, z, o_t);
-        ld(a1, B, 1, zp, o_t);
+        ld(u, B, 1, ly, o_t);
+        ld(a1, B, 1, lyp, o_t);
         {
           Raw w;
-          ld(w, B, 2, z, o_py);
+          ld(w, B, 2, ly, o_py);
           cb = G::mul(full(u), full(w));
         }
         fence();
@@ -563,15 +584,15 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
       default: {
         Raw f0, f2, v, w;
         L m;
-        ld(f0, A, 1, z, o_my);
-        ld(f2, A, 1, zp, o_my);
-        ld(w, B, 2, z, o_my);
+        ld(f0, A, 1, ly, o_my);
+        ld(f2, A, 1, lyp, o_my);
+        ld(w, B, 2, ly, o_my);
         m = G::mul(full(f0), zl(1));
         fence();
         m = G::mul_dag(m, full(f2));
         tok = link_token(m);
         fence();
-        ld(v, A, 2, z, o_my);
+        ld(v, A, 2, ly, o_my);
         Ag P = G::proj_mul_dag(m, full(w));
         fence();
         m = G::mul(full(f0), zl(0));
@@ -582,8 +603,8 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         tok = link_token(m);
         fence();
         Raw g0;
-        ld(g0, B, 1, z, o_my);
-        ld(f2, B, 1, zp, o_my);
+        ld(g0, B, 1, ly, o_my);
+        ld(f2, B, 1, lyp, o_my);
         {
           const Ag hf = hs_herm<false>(m, P);
           fence();
@@ -651,7 +672,7 @@ inline int march_chunk(int ncg, int nz, int resident) {
 template <typename G, typename T>
 void launch_semi_march(const T* A, const T* B, const Geom& g, const StepConst& c, int mode, const MarchIter& it_,
                        hipStream_t st) {
-  const int ncol = (int)(g.layer / 64);
+  const int rpw = 64 / g.nt, ncol = (g.nt + rpw - 1) / rpw;
   const int ncg = (ncol + MARCH_BS / 64 - 1) / (MARCH_BS / 64);
   MarchIter it = it_;
   it.k[0] = 0.25 / (c.a[0] * c.a[0] * c.a[1] * c.a[1]);
@@ -667,10 +688,11 @@ void launch_semi_march(const T* A, const T* B, const Geom& g, const StepConst& c
   const int lz = march_chunk(ncg, g.nz, per_cu * 256);
   const int nch = (g.nz + lz - 1) / lz;
   const dim3 grid((unsigned)(ncg * nch));
-  if (mode == 0)
-    hipLaunchKernelGGL((k_semi_march<G, T, 0>), grid, dim3(MARCH_BS), 0, st, A, B, g, it, ncg, nch, lz);
-  else
-    hipLaunchKernelGGL((k_semi_march<G, T, 1>), grid, dim3(MARCH_BS), 0, st, A, B, g, it, ncg, nch, lz);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(MARCH_BS), 0, st, A, B, g, it, ncg, nch, lz);
+  };
+  if (g.layer % RB == 0) mode == 0 ? go(k_semi_march<G, T, 0, true>) : go(k_semi_march<G, T, 1, true>);
+  else mode == 0 ? go(k_semi_march<G, T, 0, false>) : go(k_semi_march<G, T, 1, false>);
 }
 
 #define GL_MARCH_INST(G, T) \

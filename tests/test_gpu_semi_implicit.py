@@ -336,3 +336,26 @@ def test_march_chunk_lengths_agree(nc, nt, nz, reps):
     for k in ("U", "E", "rhoA", "rhoB"):
         x = b[k].reshape(*b[k].shape[:-1], reps, V)
         assert np.array_equal(x, np.broadcast_to(a[k][..., None, :], x.shape)), k
+
+
+@pytest.mark.parametrize("nc,nz,nt,dt", [(3, 5, 9, 1.0), (2, 4, 21, 0.5), (3, 3, 24, 1.0), (2, 3, 33, 1.0), (3, 2, 63, 0.5)])
+def test_march_rows_of_any_length(nc, nz, nt, dt):
+    """Rows that do not divide a wavefront (8 < nt < 64): several rows per wavefront with the last
+    one partly or wholly empty (9: seven rows, the second wavefront two; 24), one row per
+    wavefront (33, 63), layers that start inside a storage record; three steps with hops
+    against the oracle, as the parity test."""
+    pkg = lattice_or_skip()
+    w = synth.Workload(f"su{nc}-{nz}x{nt}", nc=nc, nz=nz, nt=nt, dt=dt, mu=0.5, sigma=1.0, seed=410 + nt)
+    say("case: march rows", w.name)
+    p, mv = mv_setup(w)
+    rA, rB = synth.mv_charges(w.seed, nc, nt, w.mu, w.a_T)
+    st, _ = init_mv.initial_state(rA, rB, nz, p, mv)
+    st = si.charges_for_scheme(st)
+    lat = new_lattice(pkg, w, scheme=1, max_iter=100, tol=1e-14)
+    lat.init_state(*to_comp(st), step0=0)
+    for s in range(3):
+        st = si.semi_implicit_step(st, tol=1e-14)
+        lat.step(1)
+        errs = state_errs(lat.get_state(), st)
+        say("  step", s, errs)
+        assert max(errs.values()) < 1e-10, (s, errs)
