@@ -572,17 +572,26 @@ template <typename T> struct Su3 {
   // U X U^dag
   static GL_HD Alg transport_inv(const Link& u, const Alg& x) { return sandwich<true>(u, x); }
   // principal -i Log W for W close to 1 (all eigen-angles well inside (-pi/2, pi/2)):
-  // fixed point of H <- H + proj(exp(-iH/2) W exp(-iH/2)), which converges with the
-  // cube of the symmetric-splitting error; at the fixed point W = exp(iH).
+  // fixed point of H <- H + d, d = proj(exp(-iH/2) W exp(-iH/2)); W = exp(iH) there.  Every
+  // iterate is a function of Log W, so the error e of H commutes with it and d = e - e^3/6 + ...:
+  // an update with |d|^3 below the rounding of H is the last (d is not applied twice to learn
+  // that it was).
   static GL_HD Alg logi(const Link& w) {
     Alg h = proj(w);
+    const T tol2 = sizeof(T) == 8 ? T(1e-33) : T(1e-15);   // (eps / 3)^2
     for (int it = 0; it < 40; ++it) {
-      Link hm = expi(h, T(-0.5));
-      Link R = mul(mul(hm, w), hm);
-      Alg d = proj(R);
-      T n = T(0);
-      for (int k = 0; k < 8; ++k) { h.c[k] += d.c[k]; n += d.c[k] * d.c[k]; }
-      if (n < (sizeof(T) == 8 ? T(1e-30) : T(1e-14))) break;
+      T n = T(0), m = T(0);
+      Alg d;
+      if (it == 0) {
+        // sin H = H - H^3/6: nothing to add where |H|^3 is below the rounding already
+        for (int k = 0; k < 8; ++k) m += h.c[k] * h.c[k];
+        if (m * m < tol2) break;
+      }
+      const Link hm = expi(h, T(-0.5));
+      d = proj_mul(mul(hm, w), hm);
+      m = T(0);
+      for (int k = 0; k < 8; ++k) { h.c[k] += d.c[k]; n += d.c[k] * d.c[k]; m += h.c[k] * h.c[k]; }
+      if (n * n * n <= tol2 * m) break;
     }
     return h;
   }

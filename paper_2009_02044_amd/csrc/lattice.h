@@ -212,9 +212,12 @@ template <typename T> GL_HD void link_from_stored(M3<T>& l, const T (&v)[SU3_STO
     }
   complete_row2(l);
 }
-template <typename T, typename S>
-GL_HD void store_link(const M3<T>& l, S* __restrict__ U, int i, uint32_t s, int64_t Vp) {
-  T v[SU3_STORED];
+// stored reals of a link
+template <typename T> GL_HD void stored_of(const Q2<T>& l, T (&v)[4]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = l.q[k];
+}
+template <typename T> GL_HD void stored_of(const M3<T>& l, T (&v)[SU3_STORED]) {
 #pragma unroll
   for (int r = 0; r < 2; ++r)
 #pragma unroll
@@ -222,6 +225,11 @@ GL_HD void store_link(const M3<T>& l, S* __restrict__ U, int i, uint32_t s, int6
       v[2 * (3 * r + k)] = l.re[r][k];
       v[2 * (3 * r + k) + 1] = l.im[r][k];
     }
+}
+template <typename T, typename S>
+GL_HD void store_link(const M3<T>& l, S* __restrict__ U, int i, uint32_t s, int64_t Vp) {
+  T v[SU3_STORED];
+  stored_of(l, v);
   store_comps<T, S, SU3_STORED>(v, field_dir(U, i, SU3_STORED, Vp), s);
 }
 // stored reals per link

@@ -119,21 +119,6 @@ __device__ __forceinline__ void project_near_unitary(Q2<double>& q) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) q.q[k] *= s;
 }
-// the stored reals of a link (rows 0 and 1, or the quaternion), the layout link_from_stored reads
-__device__ __forceinline__ void link_to_stored(const M3<double>& l, double (&v)[SU3_STORED]) {
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      v[2 * (3 * r + k)] = l.re[r][k];
-      v[2 * (3 * r + k) + 1] = l.im[r][k];
-    }
-}
-__device__ __forceinline__ void link_to_stored(const Q2<double>& l, double (&v)[4]) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) v[k] = l.q[k];
-}
-
 // The site's own links for an FP32 state: loaded once, projected once, their two rows kept in
 // double precision in a per-thread LDS slot (chunk q of direction d of thread t at
 // [(d NCH + q) OBS_BS + t]) and the link rebuilt from there at every use.
@@ -151,7 +136,7 @@ template <typename G> struct OwnProjLds {
       f(l, d, s);
       project_near_unitary(l);
       double v[W];
-      link_to_stored(l, v);
+      stored_of(l, v);
 #pragma unroll
       for (int q = 0; q < NCH; ++q) lds[(d * NCH + q) * OBS_BS + t] = make_double2(v[2 * q], v[2 * q + 1]);
     }

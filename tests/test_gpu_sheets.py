@@ -79,3 +79,26 @@ def test_sheet_arguments_are_checked():
         lat.init_mv(rA, rB, sigma=1.0)
     with pytest.raises(ValueError):
         lat.init_mv(rA, rB[:2], sigma=1.0)
+
+
+@pytest.mark.parametrize("nc,nz,nt,ns", [(2, 64, 15, 1), (3, 64, 16, 2), (3, 64, 17, 1), (2, 64, 33, 3), (3, 64, 2, 1)])
+def test_init_tile_edges(nc, nz, nt, ns):
+    """The initial links come in tiles of 16 x 16 transverse sites with a rim on +x and +y:
+    lattices of one short, one full and several tiles, and the smallest.  Nuclei narrow
+    enough that some layers have equal profiles at both times (farther than 38 sigma ahead of
+    one nucleus and 8.4 sigma behind the other) and others do not.  Links, E and charges
+    against the oracle to 1e-10, as the test above."""
+    pkg = lattice_or_skip()
+    w = synth.Workload(f"su{nc}-{nz}x{nt}-sheets{ns}", nc=nc, nz=nz, nt=nt, mu=0.2, sigma=0.35, seed=820 + nt)
+    print("case: initial tiles", w.name, flush=True)
+    p, mv = mv_setup(w)
+    if ns == 1:
+        rA, rB = synth.mv_charges(w.seed, nc, nt, w.mu, w.a_T)
+    else:
+        rA, rB = synth.mv_sheet_charges(w.seed, nc, nt, w.mu, w.a_T, ns)
+    st, _ = init_mv.initial_state(rA, rB, nz, p, mv)
+    lat = new_lattice(pkg, w)
+    lat.init_mv(rA, rB, m_ir=w.m_ir, uv_cut=w.uv_cut, sigma=w.sigma, zA=w.zA, zB=w.zB)
+    errs = state_errs(lat.get_state(), st)
+    print(" ", errs, flush=True)
+    assert max(errs.values()) < 1e-10, errs
