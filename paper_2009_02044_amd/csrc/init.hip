@@ -261,7 +261,7 @@ __device__ __forceinline__ double profileB(double z, double tau, const McvConst&
 constexpr int IC_TX = 16, IC_BS = IC_TX * IC_TX, IC_RIM = IC_TX + 1;
 template <typename Gd, typename T>
 __global__ void __launch_bounds__(IC_BS, 2) k_ic_links(const double* __restrict__ phi, int ns, T* __restrict__ U,
-                                                       T* __restrict__ E, Geom g, StepConst c, McvConst mv) {
+                                                       T* __restrict__ E, Geom g, StepConst c, McvConst mv, int z_first) {
   using L = typename Gd::Link;
   using A = typename Gd::Alg;
   constexpr int NG = Gd::NG, W = StoredWidth<L>::value;
@@ -273,7 +273,8 @@ __global__ void __launch_bounds__(IC_BS, 2) k_ic_links(const double* __restrict_
   const int tx = threadIdx.x % IC_TX, ty = threadIdx.x / IC_TX;
   const bool has = x0 + tx < g.nt && y0 + ty < g.nt;
   const uint32_t t = (uint32_t)(min(y0 + ty, g.nt - 1) * g.nt + min(x0 + tx, g.nt - 1));
-  if ((int)blockIdx.z == g.nz) {   // the z links of the periodic seam, in work-groups of their own
+  const int z = z_first + (int)blockIdx.z;
+  if (z == g.nz) {   // the z links of the periodic seam, in work-groups of their own
     if (!has) return;
     const double zs = (g.nz - 1) * c.a[2];
     L us[2];
@@ -293,7 +294,6 @@ __global__ void __launch_bounds__(IC_BS, 2) k_ic_links(const double* __restrict_
     store_alg(e, E, 2, s, g.Vp);
     return;
   }
-  const int z = blockIdx.z;
   const uint32_t s = (uint32_t)(z * g.layer) + t;
   auto get = [&](int p) -> L {
     double b[W];
@@ -434,7 +434,10 @@ void launch_ic_fields(const double* phi, int ns, T* U, T* E, T* rhoA, T* rhoB, c
   const int bs = 256;
   const unsigned sb = (unsigned)((g.V + bs - 1) / bs);
   const unsigned nx = (unsigned)((g.nt + IC_TX - 1) / IC_TX);
-  hipLaunchKernelGGL((k_ic_links<Gd, T>), dim3(nx, nx, (unsigned)g.nz + 1), dim3(IC_BS), 0, st, phi, ns, U, E, g, c, mv);
+  // layers 0 .. nz - 1 and the seam, as many at a time as a grid's third dimension takes
+  for (int z = 0; z <= g.nz; z += 32768)
+    hipLaunchKernelGGL((k_ic_links<Gd, T>), dim3(nx, nx, (unsigned)std::min(32768, g.nz + 1 - z)), dim3(IC_BS), 0, st,
+                       phi, ns, U, E, g, c, mv, z);
   // the semi-implicit scheme conserves D.(E + dt f1(U(t0), U(t0 - dt))) - rho instead;
   // its caller builds f1 and sets the charges through launch_gauss_charges
   if (c.scheme == 1) return;

@@ -229,7 +229,13 @@ template <typename T> GL_HD void stored_of(const M3<T>& l, T (&v)[SU3_STORED]) {
 template <typename T, typename S>
 GL_HD void store_link(const M3<T>& l, S* __restrict__ U, int i, uint32_t s, int64_t Vp) {
   T v[SU3_STORED];
-  stored_of(l, v);
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      v[2 * (3 * r + k)] = l.re[r][k];
+      v[2 * (3 * r + k) + 1] = l.im[r][k];
+    }
   store_comps<T, S, SU3_STORED>(v, field_dir(U, i, SU3_STORED, Vp), s);
 }
 // stored reals per link
