@@ -61,8 +61,8 @@ void launch_obs_gauss(const T* U, const T* E, const T* rhoA, const T* rhoB, cons
 template <typename G, typename T>
 void launch_leapfrog_observe(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const Geom& g, const StepConst& c,
                              double* partial, hipStream_t st);
-void launch_observe_finish(const double* partial, int nbx, const Geom& g, const StepConst& c, double* out,
-                           hipStream_t st);
+// slices and scalars from the partial sums of nbx work-groups per layer (added up in place)
+void launch_observe_finish(double* partial, int nbx, const Geom& g, const StepConst& c, double* out, hipStream_t st);
 // Observing step around a plain leapfrog step (any geometry and precision): launch_obs_pre on
 // the state before the step (partial sums as launch_observe; Q: obs_split_scratch_elems
 // reals of the state's precision), the step, then launch_obs_post (partial sums completed

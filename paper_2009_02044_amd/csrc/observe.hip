@@ -342,44 +342,79 @@ __global__ void __launch_bounds__(256) k_obs_gauss(const T* __restrict__ U, cons
   block_reduce_write<256>(acc, mask, partial + ((int64_t)z * nbx + slot) * NQ);
 }
 
-__global__ void __launch_bounds__(256) k_observe_finish(const double* __restrict__ partial, int nbx, Geom g,
-                                                        StepConst c, double* __restrict__ out) {
+// The partial sums of a layer's nbx work-groups added up, in place into the first one's slots: a
+// wavefront per layer, work-group partials over the lanes.
+__global__ void __launch_bounds__(256) k_observe_layers(double* __restrict__ partial, int nbx, int nz) {
+  const int z = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63u);
+  if (z >= nz) return;
+  double* p = partial + (int64_t)z * nbx * NQ;
+  double s[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) s[q] = 0.0;
+  for (int b = lane; b < nbx; b += 64)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const double v = p[(int64_t)b * NQ + q];
+      s[q] = q_is_max(q) ? fmax(s[q], v) : s[q] + v;
+    }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const double v = q_is_max(q) ? wave_max(s[q]) : wave_sum(s[q]);
+    if (lane == 0) p[q] = v;   // after every lane's loads
+  }
+}
+// Slices and scalars from each layer's nbx partial sums, the layers' first ones `stride` doubles
+// apart; one work-group.  Large lattices add the layers up beforehand (k_observe_layers):
+// alone, a layer per thread, this kernel took 39 us at 512 x 64 x 64 (16 partials a layer) and
+// 244 us at 512 x 192 x 192, its loads one after the other; the two take 15 us.  Up to a few
+// partials a layer it alone is faster (75 x 21 x 21: 4.6 us against 12).
+template <int BS>
+__global__ void __launch_bounds__(BS) k_observe_finish(const double* __restrict__ partial, int nbx, int stride, Geom g,
+                                                       StepConst c, double* __restrict__ out) {
   const int nz = g.nz;
   double loc[NQ];
+#pragma unroll
   for (int q = 0; q < NQ; ++q) loc[q] = 0.0;
   const double inv_layer = 1.0 / (double)g.layer;
-  for (int z = threadIdx.x; z < nz; z += blockDim.x) {
+  for (int z = threadIdx.x; z < nz; z += BS) {
+    const double* p = partial + (int64_t)z * stride;
     double s[NQ];
-    for (int q = 0; q < NQ; ++q) s[q] = 0.0;
-    for (int b = 0; b < nbx; ++b)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) s[q] = p[q];
+    for (int b = 1; b < nbx; ++b)
+#pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        double v = partial[((int64_t)z * nbx + b) * NQ + q];
-        s[q] = (q == 6 || q == 7) ? fmax(s[q], v) : s[q] + v;
+        const double v = p[b * NQ + q];
+        s[q] = q_is_max(q) ? fmax(s[q], v) : s[q] + v;
       }
+#pragma unroll
     for (int q = 0; q < 4; ++q) out[q * nz + z] = s[q] * inv_layer;
-    for (int q = 0; q < NQ; ++q) loc[q] = (q == 6 || q == 7) ? fmax(loc[q], s[q]) : loc[q] + s[q];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) loc[q] = q_is_max(q) ? fmax(loc[q], s[q]) : loc[q] + s[q];
   }
-  __shared__ double red[256][NQ];
-  for (int q = 0; q < NQ; ++q) red[threadIdx.x][q] = loc[q];
+  __shared__ double sum[NQ];
+  block_reduce_write<BS>(loc, Q_ALL, sum);
   __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int q = 0; q < NQ; ++q)
-        red[threadIdx.x][q] = (q == 6 || q == 7) ? fmax(red[threadIdx.x][q], red[threadIdx.x + w][q])
-                                                 : red[threadIdx.x][q] + red[threadIdx.x + w][q];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
     double* o = out + 4 * nz;
-    o[OBS_ENERGY] = c.a[0] * c.a[1] * c.a[2] * red[0][0];
-    o[OBS_GAUSS_L2] = sqrt(red[0][4]);
-    o[OBS_RHO_L2] = sqrt(red[0][5]);
-    o[OBS_GAUSS_MAX] = red[0][6];
-    o[OBS_UNITARITY] = red[0][7];
-    o[OBS_NONFINITE] = red[0][8];
-    o[OBS_GAUSS_REL] = red[0][5] > 0 ? sqrt(red[0][4] / red[0][5]) : sqrt(red[0][4]);
+    o[OBS_ENERGY] = c.a[0] * c.a[1] * c.a[2] * sum[Q_EPS];
+    o[OBS_GAUSS_L2] = sqrt(sum[Q_G2]);
+    o[OBS_RHO_L2] = sqrt(sum[Q_RHO2]);
+    o[OBS_GAUSS_MAX] = sum[Q_GMAX];
+    o[OBS_UNITARITY] = sum[Q_UNIT];
+    o[OBS_NONFINITE] = sum[Q_BAD];
+    o[OBS_GAUSS_REL] = sum[Q_RHO2] > 0 ? sqrt(sum[Q_G2] / sum[Q_RHO2]) : sqrt(sum[Q_G2]);
     o[7] = 0.0;
   }
+}
+void launch_observe_finish(double* partial, int nbx, const Geom& g, const StepConst& c, double* out, hipStream_t st) {
+  if (nbx <= 4 && g.nz <= 256) {
+    hipLaunchKernelGGL(k_observe_finish<256>, dim3(1), dim3(256), 0, st, partial, nbx, nbx * NQ, g, c, out);
+    return;
+  }
+  if (nbx > 1)
+    hipLaunchKernelGGL(k_observe_layers, dim3((unsigned)((g.nz + 3) / 4)), dim3(256), 0, st, partial, nbx, g.nz);
+  hipLaunchKernelGGL(k_observe_finish<1024>, dim3(1), dim3(1024), 0, st, partial, 1, nbx * NQ, g, c, out);
 }
 
 template <typename G, typename T>
@@ -393,7 +428,7 @@ void launch_observe(const T* U, const T* E, const T* rhoA, const T* rhoB, const 
   };
   if (rows_in_wavefronts(g.nt)) En ? go(k_observe<Gd, T, true, true>) : go(k_observe<Gd, T, true, false>);
   else En ? go(k_observe<Gd, T, false, true>) : go(k_observe<Gd, T, false, false>);
-  hipLaunchKernelGGL(k_observe_finish, dim3(1), dim3(256), 0, st, partial, nbx, g, c, out);
+  launch_observe_finish(partial, nbx, g, c, out, st);
 }
 
 // ---- partial sums of the allocation-free observables call -------------------------
@@ -438,10 +473,6 @@ void launch_obs_gauss(const T* U, const T* E, const T* rhoA, const T* rhoB, cons
   const ColMap m = col_map(g, 256);
   hipLaunchKernelGGL((k_obs_gauss<Gd, T>), dim3(col_map_blocks(g, m)), dim3(256), 0, st, U, E, rhoA, rhoB, g, c, m,
                      partial, fused_observe_blocks_per_layer(g));
-}
-void launch_observe_finish(const double* partial, int nbx, const Geom& g, const StepConst& c, double* out,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(k_observe_finish, dim3(1), dim3(256), 0, st, partial, nbx, g, c, out);
 }
 
 // ---- the observing step around a plain step (leapfrog; any geometry and precision) ----
@@ -649,7 +680,7 @@ void launch_obs_post(const T* E, const T* Q, const Geom& g, const StepConst& c, 
   using Gd = typename GroupOf<G::NC, double>::type;
   const int nbx = obs_blocks_per_layer(g);
   hipLaunchKernelGGL((k_obs_post<Gd, T>), dim3(nbx, g.nz), dim3(OBS_BS), 0, st, E, Q, g, partial);
-  hipLaunchKernelGGL(k_observe_finish, dim3(1), dim3(256), 0, st, partial, nbx, g, c, out);
+  launch_observe_finish(partial, nbx, g, c, out, st);
 }
 
 // ---- local rest frame per layer (Sec. 4) ----------------------------------------
