@@ -181,8 +181,9 @@ template <typename G> struct PlaqObs {
 };
 
 // own(l, d) sets l = U_d(x) (kept in registers or fetched again).  With OBS the forward
-// plaquettes are also handed to po.
-template <typename G, bool XS, bool OBS = false, typename F, typename OwnF, typename Obs = PlaqObs<G>>
+// plaquettes are also handed to po.  DIRS: the directions whose force is wanted (bit d), the
+// others stay zero; each comes out of the same operations in the same order, bitwise.
+template <typename G, bool XS, bool OBS = false, int DIRS = 7, typename F, typename OwnF, typename Obs = PlaqObs<G>>
 __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own, const Geom& g, Site x,
                                                  const double* inv_a2, typename G::Alg (&f)[3],
                                                  Obs* po = nullptr) {
@@ -213,6 +214,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
   const Site xmy = shifted(g, x, 1, -1), xmz = shifted(g, x, 2, -1);
   auto b_xy = [&]() {
     // plane (x, y): forward, and backward for y in -x
+    if constexpr (!(DIRS & 3)) return;
     L O0, O1, A, B;
     own(O0, 0);
     own(O1, 1);
@@ -225,6 +227,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
     acc(f[1], p, -w0);
     if constexpr (OBS) po->template plane<0>(p, tr, f[0]);
     staple_fence<OBS>();
+    if constexpr (!(DIRS & 2)) return;
     if constexpr (XS) {
       // U_{1,-0}(x) = W^dag U_{0,1}(x-x) W with W = U_0(x-x): transport the neighbour
       // lane's forward plaquette instead of forming the backward one
@@ -239,6 +242,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
   };
   auto b_xz = [&]() {
     // plane (x, z): forward, and backward for z in -x
+    if constexpr (!(DIRS & 5)) return;
     L O0, O2, A, B;
     own(O0, 0);
     own(O2, 2);
@@ -251,6 +255,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
     acc(f[2], p, -w0);
     if constexpr (OBS) po->template plane<1>(p, tr, f[0]);   // f_x complete
     staple_fence<OBS>();
+    if constexpr (!(DIRS & 4)) return;
     if constexpr (XS) {
       acc(f[2], G::transport(pull_link(O0, xn.am), pull_alg(p, xn.am)), w0);
     } else {
@@ -263,6 +268,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
   };
   auto b_yz = [&]() {
     // plane (y, z): forward
+    if constexpr (!(DIRS & 6)) return;
     L O1, O2, A, B;
     own(O1, 1);
     own(O2, 2);
@@ -278,33 +284,43 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
   };
   auto b_my = [&]() {
     // backward in -y for x and z, sharing U_1(x-y)
+    if constexpr (!(DIRS & 5)) return;
     L Y1, O, A, B;
     fetch(Y1, 1, idx(g, xmy));                                // U_1(x-y)
-    fetch(B, 0, idx(g, xmy));                                 // U_0(x-y)
-    own(O, 0);
-    A = xs(Y1, xmy, 1, +1);                                   // U_1(x+x-y)
-    acc(f[0], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Y1), w1);
-    staple_fence<OBS>();
-    own(O, 2);
-    fetch(A, 1, idx(g, shifted(g, xpz, 1, -1)));              // U_1(x+z-y)
-    fetch(B, 2, idx(g, xmy));                                 // U_2(x-y)
-    acc(f[2], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Y1), w1);
-    staple_fence<OBS>();
+    if constexpr (DIRS & 1) {
+      fetch(B, 0, idx(g, xmy));                               // U_0(x-y)
+      own(O, 0);
+      A = xs(Y1, xmy, 1, +1);                                 // U_1(x+x-y)
+      acc(f[0], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Y1), w1);
+      staple_fence<OBS>();
+    }
+    if constexpr (DIRS & 4) {
+      own(O, 2);
+      fetch(A, 1, idx(g, shifted(g, xpz, 1, -1)));            // U_1(x+z-y)
+      fetch(B, 2, idx(g, xmy));                               // U_2(x-y)
+      acc(f[2], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Y1), w1);
+      staple_fence<OBS>();
+    }
   };
   auto b_mz = [&]() {
     // backward in -z for x and y, sharing U_2(x-z)
+    if constexpr (!(DIRS & 3)) return;
     L Z2, O, A, B;
     fetch(Z2, 2, idx(g, xmz));                                // U_2(x-z)
-    fetch(B, 0, idx(g, xmz));                                 // U_0(x-z)
-    own(O, 0);
-    A = xs(Z2, xmz, 2, +1);                                   // U_2(x+x-z)
-    acc(f[0], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Z2), w2);
-    staple_fence<OBS>();
-    own(O, 1);
-    fetch(A, 2, idx(g, shifted(g, xpy, 2, -1)));              // U_2(x+y-z)
-    fetch(B, 1, idx(g, xmz));                                 // U_1(x-z)
-    acc(f[1], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Z2), w2);
-    staple_fence<OBS>();
+    if constexpr (DIRS & 1) {
+      fetch(B, 0, idx(g, xmz));                               // U_0(x-z)
+      own(O, 0);
+      A = xs(Z2, xmz, 2, +1);                                 // U_2(x+x-z)
+      acc(f[0], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Z2), w2);
+      staple_fence<OBS>();
+    }
+    if constexpr (DIRS & 2) {
+      own(O, 1);
+      fetch(A, 2, idx(g, shifted(g, xpy, 2, -1)));            // U_2(x+y-z)
+      fetch(B, 1, idx(g, xmz));                               // U_1(x-z)
+      acc(f[1], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Z2), w2);
+      staple_fence<OBS>();
+    }
   };
   // Order of the plaquette groups (the force sums in this order).  The -z group first:
   // its links of layer z - 1 are then loaded while the work-groups of that layer load

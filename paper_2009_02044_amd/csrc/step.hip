@@ -13,6 +13,7 @@
 //   B (+z): rho_B(x+z) <- U_z^dag(x) rho_B(x) U_z(x),     j_z(x) -= (a_L/dt) rho_B(x)
 //   A (-z): rho_A(x)   <- U_z(x) rho_A(x+z) U_z^dag(x),   j_z(x) += (a_L/dt) rho_A'(x)
 // With co-moving charge storage both rewrites are in place (one slot per thread).
+#include <type_traits>
 #include "internal.h"
 #include "stencil.h"
 #include "reduce.h"
@@ -221,21 +222,66 @@ __global__ void __launch_bounds__(LF_BS, OBS ? 2 : GL_LF_WAVES) k_leapfrog(const
   }
 }
 
+// One thread per link (blockIdx.y: direction), for lattices that leave most of the chip idle
+// with a thread per site: the serial work of a thread, which decides there, is 0.4 of the
+// site's.  Each link's force comes out of the same operations in the same order as the site
+// kernel's, so the state does not depend on which of the two runs (bitwise).
+constexpr int LF_LINK_BS = 64;
+template <typename G, typename T, bool HOP, bool XS, bool RU, int D>
+__device__ __forceinline__ void update_link(const T* __restrict__ U, T* __restrict__ Unew, T* __restrict__ E,
+                                            T* __restrict__ rhoA, T* __restrict__ rhoB, const Geom& g,
+                                            const StepConst& c, const double* inv_a2, Site x, uint32_t s) {
+  const GlobalLinks<T> fetch{U, g.Vp};
+  const OwnLinks<G, T, OWN_REGS> own(fetch, s, nullptr, 0, 0);
+  typename G::Alg f[3];
+  plaquette_forces<G, XS, false, 1 << D>(fetch, own, g, x, inv_a2, f);
+  finish_link<G, T, HOP>(own.O[D], f[D], Unew, E, rhoA, rhoB, g, c, x, s, D, RU);
+}
+template <typename G, typename T, bool HOP, bool XS, bool RU>
+__global__ void __launch_bounds__(LF_LINK_BS) k_leapfrog_link(const T* __restrict__ U, T* __restrict__ Unew,
+                                                              T* __restrict__ E, T* __restrict__ rhoA,
+                                                              T* __restrict__ rhoB, Geom g, StepConst c, ColMap m) {
+  Site x;
+  uint32_t s;
+  if (!col_map_site(g, m, blockIdx.x, threadIdx.x, LF_LINK_BS, x, s)) return;
+  const double inv_a2[3] = {1.0 / (c.a[0] * c.a[0]), 1.0 / (c.a[1] * c.a[1]), 1.0 / (c.a[2] * c.a[2])};
+  if (blockIdx.y == 0) update_link<G, T, false, XS, RU, 0>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s);
+  else if (blockIdx.y == 1) update_link<G, T, false, XS, RU, 1>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s);
+  else update_link<G, T, HOP, XS, RU, 2>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s);
+}
+
+// Sites up to which a thread per link is taken: where the two kernels take the same time.  Per
+// step, site against link kernel: 64 x 8 x 8 SU(2) FP64 6.3 / 3.9 us, SU(3) FP64 13.7 / 7.2 us, FP32
+// 12.3 / 6.4 us; 75 x 21 x 21 SU(3) FP64 18.3 / 16.3 us, FP32 15.4 / 9.5 us; SU(3) FP64 36 864 sites
+// 18.7 / 17.2 us, 49 152 20.9 / 23.0 us; the others 81 920 sites 7.5-19.4 / 6.6-18.2 us, 114 688
+// 8.1-23.1 / 8.5-24.5 us.  (SU(3) in double precision takes the registers of a whole SIMD lane.)
+template <typename G, typename T> constexpr int64_t LF_LINK_MAX = G::NC == 3 && sizeof(T) == 8 ? 40960 : 81920;
+
 template <typename G, typename T>
 void launch_leapfrog(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const Geom& g, const StepConst& c,
                      bool reunit, hipStream_t st) {
-  const int bs = LF_BS;
-  const ColMap m = col_map(g, bs);
-  const dim3 grid(col_map_blocks(g, m));
   // rows inside wavefronts: x neighbours from other lanes
   const bool xs = rows_in_wavefronts(g.nt);
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(bs), 0, st, U, Unew, E, rhoA, rhoB, g, c, m, nullptr); };
+  const bool link = g.V <= LF_LINK_MAX<G, T>;
+  const int bs = link ? LF_LINK_BS : LF_BS;
+  const ColMap m = col_map(g, bs);
+  const dim3 grid(col_map_blocks(g, m), link ? 3 : 1);
+  auto pick = [&](auto hop, auto xn, auto ru) {
+    constexpr bool H = decltype(hop)::value, X = decltype(xn)::value, R = decltype(ru)::value;
+    if (link)
+      hipLaunchKernelGGL((k_leapfrog_link<G, T, H, X, R>), grid, dim3(bs), 0, st, U, Unew, E, rhoA, rhoB, g, c, m);
+    else
+      hipLaunchKernelGGL((k_leapfrog<G, T, H, X, false, R>), grid, dim3(bs), 0, st, U, Unew, E, rhoA, rhoB, g, c, m,
+                         nullptr);
+  };
+  using Y = std::true_type;
+  using N = std::false_type;
   if (!reunit) {
-    if (c.hop) xs ? go(k_leapfrog<G, T, true, true>) : go(k_leapfrog<G, T, true, false>);
-    else xs ? go(k_leapfrog<G, T, false, true>) : go(k_leapfrog<G, T, false, false>);
+    if (c.hop) xs ? pick(Y{}, Y{}, N{}) : pick(Y{}, N{}, N{});
+    else xs ? pick(N{}, Y{}, N{}) : pick(N{}, N{}, N{});
   } else {
-    if (c.hop) xs ? go(k_leapfrog<G, T, true, true, false, true>) : go(k_leapfrog<G, T, true, false, false, true>);
-    else xs ? go(k_leapfrog<G, T, false, true, false, true>) : go(k_leapfrog<G, T, false, false, false, true>);
+    if (c.hop) xs ? pick(Y{}, Y{}, Y{}) : pick(Y{}, N{}, Y{});
+    else xs ? pick(N{}, Y{}, Y{}) : pick(N{}, N{}, Y{});
   }
 }
 

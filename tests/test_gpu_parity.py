@@ -576,3 +576,31 @@ def test_dispersion_relation_of_small_plane_waves(nt, k):
     expect = 1 - dt ** 2 * Om2 / 2
     say("  cos(w dt)", float(np.mean(cos_w)), "closed form", expect, "max dev", float(np.abs(cos_w - expect).max()))
     np.testing.assert_allclose(cos_w, expect, rtol=1e-8, atol=1e-9)
+
+
+@pytest.mark.parametrize("nc,fp,nt", [(2, 64, 16), (2, 32, 21), (3, 64, 21), (3, 32, 16), (3, 64, 64), (3, 32, 2)])
+def test_link_and_site_steps_agree(nc, fp, nt):
+    """Small lattices take a step with a thread per link, larger ones with a thread per site: nz
+    layers against the same layers repeated along z until the other kernel runs.  Same
+    operations in the same order: bitwise equal, through hops, no-hop steps and (FP32)
+    reunitarising steps, with rows in wavefronts (2, 16, 64) and across them (21)."""
+    pkg = lattice_or_skip()
+    nz = 4
+    reps = 90000 // (nz * nt * nt) + 1
+    w = synth.Workload(f"su{nc}-{nz}x{nt}", nc=nc, nz=nz, nt=nt, mu=0.5, sigma=0.8, seed=430 + nt)
+    print("case: link and site steps", w.name, "fp", fp, "x", reps, flush=True)
+    p, mv = mv_setup(w)
+    rA, rB = synth.mv_charges(w.seed, nc, nt, w.mu, w.a_T)
+    st, _ = init_mv.initial_state(rA, rB, nz, p, mv)
+    arrs = to_comp(st)
+    V = nz * nt * nt
+    kw = dict(nc=nc, nt=nt, a_T=w.a_T, a_L=w.a_L, dt=w.dt, fp=fp, reunit_every=4 if fp == 32 else 0)
+    one, many = pkg.Lattice(nz=nz, **kw), pkg.Lattice(nz=nz * reps, **kw)
+    one.init_state(*arrs, step0=0)
+    many.init_state(*[np.tile(x, reps) for x in arrs], step0=0)
+    one.step(6)
+    many.step(6)
+    a, b = one.get_state(), many.get_state()
+    for k in ("U", "E", "rhoA", "rhoB"):
+        x = b[k].reshape(*b[k].shape[:-1], reps, V)
+        assert np.array_equal(x, np.broadcast_to(a[k][..., None, :], x.shape)), k
