@@ -604,3 +604,24 @@ def test_link_and_site_steps_agree(nc, fp, nt):
     for k in ("U", "E", "rhoA", "rhoB"):
         x = b[k].reshape(*b[k].shape[:-1], reps, V)
         assert np.array_equal(x, np.broadcast_to(a[k][..., None, :], x.shape)), k
+
+
+@pytest.mark.parametrize("nc,nz,nt", [(2, 9, 100), (3, 5, 100), (2, 6, 128)])
+def test_step_of_layers_in_bands(nc, nz, nt):
+    """Layers of more than 9216 sites are swept in bands (the last one narrower at nt = 100): two
+    steps against the oracle; an observing step between them (fused at nt = 128)."""
+    pkg = lattice_or_skip()
+    w = synth.Workload(f"su{nc}-{nz}x{nt}", nc=nc, nz=nz, nt=nt, mu=0.5, sigma=1.0, seed=440 + nt)
+    say("case: layers in bands", w.name)
+    p, mv = mv_setup(w)
+    rA, rB = synth.mv_charges(w.seed, nc, nt, w.mu, w.a_T)
+    st, _ = init_mv.initial_state(rA, rB, nz, p, mv)
+    lat = new_lattice(pkg, w)
+    lat.init_state(*to_comp(st), step0=0)
+    buf = lat.obs_buffer()
+    lat.step_observe(2, buf)
+    st = lattice.leapfrog_step(st)
+    _obs_close(pkg.Lattice.unpack_obs(buf, nz), observables.observables(st), 1e-8)
+    st = lattice.leapfrog_step(st)
+    errs = state_errs(lat.get_state(), st)
+    assert max(errs.values()) < 1e-10, errs
