@@ -364,36 +364,43 @@ __global__ void __launch_bounds__(256) k_observe_layers(double* __restrict__ par
   }
 }
 // Slices and scalars from each layer's nbx partial sums, the layers' first ones `stride` doubles
-// apart; one work-group.  Large lattices add the layers up beforehand (k_observe_layers):
-// alone, a layer per thread, this kernel took 39 us at 512 x 64 x 64 (16 partials a layer) and
-// 244 us at 512 x 192 x 192, its loads one after the other; the two take 15 us.  Up to a few
-// partials a layer it alone is faster (75 x 21 x 21: 4.6 us against 12).
-template <int BS>
-__global__ void __launch_bounds__(BS) k_observe_finish(const double* __restrict__ partial, int nbx, int stride, Geom g,
-                                                       StepConst c, double* __restrict__ out) {
+// apart; one work-group, P = 2^lp lanes per layer.  Its loads one after the other
+// decide (0.6 us each, a work-group of 1024 threads costs 2.7 us more than it saves up to 1500
+// layers).
+constexpr int OBS_FIN_BS = 256;
+__global__ void __launch_bounds__(OBS_FIN_BS) k_observe_finish(const double* __restrict__ partial, int nbx, int stride,
+                                                               int lp, Geom g, StepConst c, double* __restrict__ out) {
   const int nz = g.nz;
   double loc[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) loc[q] = 0.0;
   const double inv_layer = 1.0 / (double)g.layer;
-  for (int z = threadIdx.x; z < nz; z += BS) {
+  const int P = 1 << lp, lane = (int)threadIdx.x & (P - 1);
+  for (int z = (int)threadIdx.x >> lp; z < nz; z += OBS_FIN_BS >> lp) {
     const double* p = partial + (int64_t)z * stride;
     double s[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) s[q] = p[q];
-    for (int b = 1; b < nbx; ++b)
+    for (int q = 0; q < NQ; ++q) s[q] = 0.0;   // (the maxima are of absolute values)
+    for (int b = lane; b < nbx; b += P)
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
         const double v = p[b * NQ + q];
         s[q] = q_is_max(q) ? fmax(s[q], v) : s[q] + v;
       }
+    for (int o = P / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const double v = __shfl_xor(s[q], o);
+        s[q] = q_is_max(q) ? fmax(s[q], v) : s[q] + v;
+      }
+    if (lane) continue;
 #pragma unroll
     for (int q = 0; q < 4; ++q) out[q * nz + z] = s[q] * inv_layer;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) loc[q] = q_is_max(q) ? fmax(loc[q], s[q]) : loc[q] + s[q];
   }
   __shared__ double sum[NQ];
-  block_reduce_write<BS>(loc, Q_ALL, sum);
+  block_reduce_write<OBS_FIN_BS>(loc, Q_ALL, sum);
   __syncthreads();
   if (threadIdx.x == 0) {
     double* o = out + 4 * nz;
@@ -407,14 +414,21 @@ __global__ void __launch_bounds__(BS) k_observe_finish(const double* __restrict_
     o[7] = 0.0;
   }
 }
+// One kernel, as many lanes per layer as the work-group has, unless that leaves a lane more than 8
+// loads above those of one partial per layer: the layers are then added up beforehand.  Both
+// kernels against one, SU(2) FP32, the whole pass: 300 x 20 x 20 27.5 / 23.8 us, 256 x 48 x 48
+// (8 loads) 52.9 / 53.3 us, 512 x 48 x 48 90.1 / 95.1 us; before, alone with a lane per layer,
+// 39 us of 512 x 64 x 64's and 244 us of 512 x 192 x 192's pass went here, with both kernels 15 us.
 void launch_observe_finish(double* partial, int nbx, const Geom& g, const StepConst& c, double* out, hipStream_t st) {
-  if (nbx <= 4 && g.nz <= 256) {
-    hipLaunchKernelGGL(k_observe_finish<256>, dim3(1), dim3(256), 0, st, partial, nbx, nbx * NQ, g, c, out);
-    return;
-  }
-  if (nbx > 1)
+  int lp = 0;
+  while ((1 << lp) < nbx && lp < 6 && (int64_t)2 * g.nz << lp <= OBS_FIN_BS) ++lp;
+  const int64_t one = (g.nz + OBS_FIN_BS - 1) / OBS_FIN_BS;
+  const int64_t loads = (int64_t)((nbx + (1 << lp) - 1) >> lp) * one;   // one after the other (lp > 0: one = 1)
+  const bool both = loads - one > 8;
+  if (both)
     hipLaunchKernelGGL(k_observe_layers, dim3((unsigned)((g.nz + 3) / 4)), dim3(256), 0, st, partial, nbx, g.nz);
-  hipLaunchKernelGGL(k_observe_finish<1024>, dim3(1), dim3(1024), 0, st, partial, 1, nbx * NQ, g, c, out);
+  hipLaunchKernelGGL(k_observe_finish, dim3(1), dim3(OBS_FIN_BS), 0, st, partial, both ? 1 : nbx, nbx * NQ,
+                     both ? 0 : lp, g, c, out);
 }
 
 template <typename G, typename T>

@@ -625,3 +625,21 @@ def test_step_of_layers_in_bands(nc, nz, nt):
     st = lattice.leapfrog_step(st)
     errs = state_errs(lat.get_state(), st)
     assert max(errs.values()) < 1e-10, errs
+
+
+@pytest.mark.parametrize("nz,nt", [(129, 49), (129, 48), (128, 49), (5, 49), (2, 200)])
+def test_observables_over_partial_sums(nz, nt):
+    """The observables' partial sums: 10 of a layer added up beforehand (129 x 49), 9 by a lane
+    (129 x 48), over 2 lanes, over 16 and over 64: slices and scalars against the oracle."""
+    pkg = lattice_or_skip()
+    say("case: partial sums", nz, nt)
+    p = lattice.Params(nc=2, a_T=4.0, a_L=1.0, dt=0.5)
+    st = init_mv.state_from_algebra(synth.normal(600 + nt, (3, nz, nt, nt, 3), 0.6),
+                                    synth.normal(700 + nt, (3, nz, nt, nt, 3), 0.3), p)
+    lat = pkg.Lattice(nc=2, nz=nz, nt=nt, a_T=4.0, a_L=1.0, dt=0.5, fp=64)
+    lat.init_state(*to_comp(st), step0=0)
+    go, oo = lat.observables(), observables.observables(st)
+    _obs_close(go, oo, 1e-11)
+    for k in ("gauss_l2", "rho_l2", "gauss_max"):
+        if k in oo:
+            assert abs(go[k] - oo[k]) <= 1e-11 * abs(oo[k]) + 1e-14, k
