@@ -57,6 +57,9 @@ template <typename T> struct Su2 {
   static GL_HD Link dag(const Link& a) { Link r; r.q[0] = a.q[0]; r.q[1] = -a.q[1]; r.q[2] = -a.q[2]; r.q[3] = -a.q[3]; return r; }
   static GL_HD Link mul_dag(const Link& a, const Link& b) { return mul(a, dag(b)); }   // a b^dag
   static GL_HD Link dag_mul(const Link& a, const Link& b) { return mul(dag(a), b); }   // a^dag b
+  // a b c^dag and a b^dag c^dag of group elements
+  static GL_HD Link chain(const Link& a, const Link& b, const Link& c) { return mul_dag(mul(a, b), c); }
+  static GL_HD Link chain_dag(const Link& a, const Link& b, const Link& c) { return mul_dag(a, mul(c, b)); }
   static GL_HD void add_to(Link& acc, const Link& a, T s) { for (int k = 0; k < 4; ++k) acc.q[k] += s * a.q[k]; }
   static GL_HD void acc_mul_dag(Link& r, const Link& a, const Link& b) { add_to(r, mul_dag(a, b), T(1)); }
   static GL_HD void acc_dag_mul(Link& r, const Link& a, const Link& b) { add_to(r, dag_mul(a, b), T(1)); }
@@ -129,6 +132,26 @@ template <typename T> struct Su2 {
   }
 };
 
+// Row 2 of a special unitary matrix from rows 0 and 1: u_2k = conj(u_0a u_1b - u_0b u_1a),
+// (a, b) = (k+1, k+2) mod 3; each real part one fused chain.
+template <typename T>
+GL_HD void complete_row2(M3<T>& l) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int a = (k + 1) % 3, b = (k + 2) % 3;
+    T cr = l.re[0][a] * l.re[1][b];
+    cr = fmx(-l.im[0][a], l.im[1][b], cr);
+    cr = fmx(-l.re[0][b], l.re[1][a], cr);
+    cr = fmx(l.im[0][b], l.im[1][a], cr);
+    T ci = l.re[0][a] * l.im[1][b];
+    ci = fmx(l.im[0][a], l.re[1][b], ci);
+    ci = fmx(-l.re[0][b], l.im[1][a], ci);
+    ci = fmx(-l.im[0][b], l.re[1][a], ci);
+    l.re[2][k] = cr;
+    l.im[2][k] = -ci;
+  }
+}
+
 // ----------------------------------------------------------------------------
 // SU(3)
 // ----------------------------------------------------------------------------
@@ -154,10 +177,12 @@ template <typename T> struct Su3 {
   // re/im of the k-th term: (x y)  -> xr yr - xi yi, xr yi + xi yr
   //                          (x y*) -> xr yr + xi yi, xi yr - xr yi
   //                          (x* y) -> xr yr + xi yi, xr yi - xi yr
-  static GL_HD Link mul(const Link& a, const Link& b) {
-    Link r;
+  static GL_HD Link mul(const Link& a, const Link& b) { Link r; mul_into<3>(r, a, b); return r; }
+  // the first NR rows of a b
+  template <int NR>
+  static GL_HD void mul_into(Link& r, const Link& a, const Link& b) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         T sr = a.re[i][0] * b.re[0][j], si = a.re[i][0] * b.im[0][j];
@@ -172,13 +197,12 @@ template <typename T> struct Su3 {
         }
         r.re[i][j] = sr; r.im[i][j] = si;
       }
-    return r;
   }
-  // r (+)= a b^dag: (a b^dag)_ij = sum_k a_ik conj(b_jk)
-  template <bool ACC>
+  // r (+)= a b^dag, its first NR rows: (a b^dag)_ij = sum_k a_ik conj(b_jk)
+  template <bool ACC, int NR = 3>
   static GL_HD void mul_dag_into(Link& r, const Link& a, const Link& b) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         T sr, si;
@@ -230,6 +254,22 @@ template <typename T> struct Su3 {
   }
   static GL_HD Link mul_dag(const Link& a, const Link& b) { Link r; mul_dag_into<false>(r, a, b); return r; }
   static GL_HD Link dag_mul(const Link& a, const Link& b) { Link r; dag_mul_into<false>(r, a, b); return r; }
+  // a b c^dag and a b^dag c^dag of group elements: two rows of each product (which need two rows
+  // of a), the third one of the result rebuilt as for a stored link; 168 multiply-adds for 216
+  static GL_HD Link chain(const Link& a, const Link& b, const Link& c) {
+    Link m, r;
+    mul_into<2>(m, a, b);
+    mul_dag_into<false, 2>(r, m, c);
+    complete_row2(r);
+    return r;
+  }
+  static GL_HD Link chain_dag(const Link& a, const Link& b, const Link& c) {
+    Link m, r;
+    mul_dag_into<false, 2>(m, a, b);
+    mul_dag_into<false, 2>(r, m, c);
+    complete_row2(r);
+    return r;
+  }
   static GL_HD void acc_mul_dag(Link& r, const Link& a, const Link& b) { mul_dag_into<true>(r, a, b); }
   static GL_HD void acc_dag_mul(Link& r, const Link& a, const Link& b) { dag_mul_into<true>(r, a, b); }
   static GL_HD void scale(Link& r, T s) {

@@ -171,6 +171,7 @@ template <typename A> __device__ __forceinline__ A pull_alg(const A& v, int a) {
 // or U_{y,z}, with the force term that is complete at that point (f_x for K = 1, f_y
 // for K = 2; see the group order below).  PlaqObs keeps them for later use.
 template <typename G> struct PlaqObs {
+  static constexpr bool UNITARY = false;
   typename G::Alg p[3];
   typename G::Real tr[3];
   template <int K>
@@ -208,6 +209,15 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
 #pragma unroll
     for (int k = 0; k < NG; ++k) a.c[k] = fmx(w, p.c[k], a.c[k]);
   };
+  // a b c^dag, a (c b)^dag
+  auto chain = [](const L& a, const L& b, const L& c) -> L {
+    if constexpr (OBS && Obs::UNITARY) return G::chain(a, b, c);
+    else return G::mul_dag(G::mul(a, b), c);
+  };
+  auto chain_dag = [](const L& a, const L& b, const L& c) -> L {
+    if constexpr (OBS && Obs::UNITARY) return G::chain_dag(a, b, c);
+    else return G::mul_dag(a, G::mul(c, b));
+  };
 #pragma unroll
   for (int i = 0; i < 3; ++i) f[i] = G::alg_zero();
   const Site xpy = shifted(g, x, 1, +1), xpz = shifted(g, x, 2, +1);
@@ -220,7 +230,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
     own(O1, 1);
     fetch(B, 0, idx(g, xpy));                                 // U_0(x+y)
     A = xs(O1, x, 1, +1);                                     // U_1(x+x)
-    const L M2 = G::mul_dag(G::mul(O0, A), B);
+    const L M2 = chain(O0, A, B);
     R tr = R(0);
     const Ag p = OBS ? G::proj_retr_mul_dag(M2, O1, tr) : G::proj_mul_dag(M2, O1);
     acc(f[0], p, w1);
@@ -236,7 +246,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
       const L A2 = xs(B, xpy, 0, -1);                         // U_0(x+y-x)
       const L B2 = xs(O1, x, 1, -1);                          // U_1(x-x)
       const L C2 = xs(O0, x, 0, -1);                          // U_0(x-x)
-      acc(f[1], G::proj_mul(G::mul_dag(O1, G::mul(B2, A2)), C2), w0);
+      acc(f[1], G::proj_mul(chain_dag(O1, A2, B2), C2), w0);
     }
     staple_fence<OBS>();
   };
@@ -248,7 +258,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
     own(O2, 2);
     fetch(B, 0, idx(g, xpz));                                 // U_0(x+z)
     A = xs(O2, x, 2, +1);                                     // U_2(x+x)
-    const L M2 = G::mul_dag(G::mul(O0, A), B);
+    const L M2 = chain(O0, A, B);
     R tr = R(0);
     const Ag p = OBS ? G::proj_retr_mul_dag(M2, O2, tr) : G::proj_mul_dag(M2, O2);
     acc(f[0], p, w2);
@@ -262,7 +272,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
       const L A2 = xs(B, xpz, 0, -1);                         // U_0(x+z-x)
       const L B2 = xs(O2, x, 2, -1);                          // U_2(x-x)
       const L C2 = xs(O0, x, 0, -1);                          // U_0(x-x)
-      acc(f[2], G::proj_mul(G::mul_dag(O2, G::mul(B2, A2)), C2), w0);
+      acc(f[2], G::proj_mul(chain_dag(O2, A2, B2), C2), w0);
     }
     staple_fence<OBS>();
   };
@@ -274,7 +284,7 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
     own(O2, 2);
     fetch(A, 2, idx(g, xpy));                                 // U_2(x+y)
     fetch(B, 1, idx(g, xpz));                                 // U_1(x+z)
-    const L M2 = G::mul_dag(G::mul(O1, A), B);
+    const L M2 = chain(O1, A, B);
     R tr = R(0);
     const Ag p = OBS ? G::proj_retr_mul_dag(M2, O2, tr) : G::proj_mul_dag(M2, O2);
     acc(f[1], p, w2);
@@ -291,14 +301,14 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
       fetch(B, 0, idx(g, xmy));                               // U_0(x-y)
       own(O, 0);
       A = xs(Y1, xmy, 1, +1);                                 // U_1(x+x-y)
-      acc(f[0], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Y1), w1);
+      acc(f[0], G::proj_mul(chain_dag(O, A, B), Y1), w1);
       staple_fence<OBS>();
     }
     if constexpr (DIRS & 4) {
       own(O, 2);
       fetch(A, 1, idx(g, shifted(g, xpz, 1, -1)));            // U_1(x+z-y)
       fetch(B, 2, idx(g, xmy));                               // U_2(x-y)
-      acc(f[2], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Y1), w1);
+      acc(f[2], G::proj_mul(chain_dag(O, A, B), Y1), w1);
       staple_fence<OBS>();
     }
   };
@@ -311,14 +321,14 @@ __device__ __forceinline__ void plaquette_forces(const F& fetch, const OwnF& own
       fetch(B, 0, idx(g, xmz));                               // U_0(x-z)
       own(O, 0);
       A = xs(Z2, xmz, 2, +1);                                 // U_2(x+x-z)
-      acc(f[0], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Z2), w2);
+      acc(f[0], G::proj_mul(chain_dag(O, A, B), Z2), w2);
       staple_fence<OBS>();
     }
     if constexpr (DIRS & 2) {
       own(O, 1);
       fetch(A, 2, idx(g, shifted(g, xpy, 2, -1)));            // U_2(x+y-z)
       fetch(B, 1, idx(g, xmz));                               // U_1(x-z)
-      acc(f[1], G::proj_mul(G::mul_dag(O, G::mul(B, A)), Z2), w2);
+      acc(f[1], G::proj_mul(chain_dag(O, A, B), Z2), w2);
       staple_fence<OBS>();
     }
   };

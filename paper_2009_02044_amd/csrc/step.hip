@@ -46,6 +46,7 @@ constexpr int LF_BS = 256;
 // there, with E_i(t + dt/2) computed as the link update computes it, so that no
 // projection stays live until the link update.
 template <typename G, typename T> struct ObsAcc {
+  static constexpr bool UNITARY = false;   // links as stored
   double EL2 = 0.0, ET2 = 0.0, sl = 0.0;
   bool bad = false;
   const T* E;
