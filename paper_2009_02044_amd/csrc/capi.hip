@@ -1314,7 +1314,6 @@ static int adjoint_reverse(glasma_ctx* c, void* work, size_t work_bytes, Seed&& 
     const StatePtr fin = ckpt(a.nseg);
     int r = seed.template operator()<G, T>(fin, lam, ebar, rA[0], rB[0], part);
     if (r) return r;
-    const size_t nE = 3 * (size_t)c->ng * c->g.Vp * sizeof(T), nR = (size_t)c->ng * c->g.Vp * sizeof(T);
     if (steps > 0) launch_adj_ra<G, T>((const T*)fin.E, c->g, sp, c->p.dt, lam, ebar, c->stream);
     for (int64_t k = a.nseg - 1; k >= 0; --k) {
       const int64_t sk = s0 + k * every;
@@ -1324,18 +1323,22 @@ static int adjoint_reverse(glasma_ctx* c, void* work, size_t work_bytes, Seed&& 
         if (m == len) return ckpt(k + 1);
         return state_at(a, w + a.seg + (size_t)(m - 1) * a.state);
       };
-      // recompute the segment's states (bitwise those of the forward pass)
+      // Recompute the segment's states (bitwise those of the forward pass), each step from one
+      // state's fields into the next one's.  The charges change on hops only: rho[m] is the
+      // state that holds those of slot(m).  (Steps in place on copied fields: three copies of
+      // 5.6 us per step of 36-44 us at 256 x 32 x 32 SU(3) FP32.)
+      std::vector<StatePtr> rho(len, slot(0));
       for (int64_t m = 0; m + 1 < len; ++m) {
         const StatePtr x = slot(m), y = slot(m + 1);
-        HIPCHK(c, hipMemcpyAsync(y.E, x.E, nE, hipMemcpyDeviceToDevice, c->stream));
-        HIPCHK(c, hipMemcpyAsync(y.rA, x.rA, nR, hipMemcpyDeviceToDevice, c->stream));
-        HIPCHK(c, hipMemcpyAsync(y.rB, x.rB, nR, hipMemcpyDeviceToDevice, c->stream));
         StepConst sc;
         sc.a[0] = sp[0]; sc.a[1] = sp[1]; sc.a[2] = sp[2];
         sc.dt = c->p.dt;
         sc.hop = is_hop(c, sk + m) ? 1 : 0;
         sc.offA = sc.offB = off_at(c, s0, off0, sk + m);
         sc.scheme = 0;
+        sc.from_E = (const T*)x.E - (const T*)y.E;
+        sc.from_rho = (const T*)rho[m].rA - (const T*)y.rA;   // the same for rho_B
+        rho[m + 1] = sc.hop ? y : rho[m];
         const bool ru = c->p.reunit_every > 0 && (sk + m + 1) % c->p.reunit_every == 0;
         launch_leapfrog<G, T>((const T*)x.U, (T*)y.U, (T*)y.E, (T*)y.rA, (T*)y.rB, c->g, sc, ru, c->stream);
       }
@@ -1343,7 +1346,7 @@ static int adjoint_reverse(glasma_ctx* c, void* work, size_t work_bytes, Seed&& 
         const int64_t s = sk + m;
         const StatePtr x = slot(m), y = slot(m + 1);
         const bool hop = is_hop(c, s);
-        launch_adj_step<G, T>((const T*)x.U, (const T*)x.E, (const T*)y.rA, (const T*)x.rB,
+        launch_adj_step<G, T>((const T*)x.U, (const T*)x.E, (const T*)y.rA, (const T*)rho[m].rB,
                               off_at(c, s0, off0, s + 1), off_at(c, s0, off0, s), hop, s > s0, c->g, sp, c->p.dt,
                               lam, ebar, K, rA[cur], rB[cur], rA[cur ^ 1], rB[cur ^ 1], c->stream);
         if (hop) cur ^= 1;
