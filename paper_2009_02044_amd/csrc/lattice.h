@@ -286,13 +286,12 @@ struct ColMap {
   int slab;      // 1: slab decomposition
   int band;      // slabs: blocks per band, a band swept through the slab before the next
 };
-// Sites of a band.  A CU array in flight covers ~32 000 sites of an XCD; in bands of a few rows
-// these are several layers, so most links loaded as z +- 1 neighbours are in the L2 then, and in
-// whole layers of more than that none are.  Per step, whole layers against bands of at most
-// 4096 / 6144 / 9216 sites: 512 x 192 x 192 SU(3) FP32 2854 us against 2705 / 2703 / 2695,
-// 256 x 192 x 192 SU(2) FP64 910 against 875 / 870 / 869, 128 x 150 x 150 SU(3) FP64 877 against
-// 825 / 822 / 835; layers of up to 9216 sites are as fast whole (1024 x 96 x 96 SU(2) FP64 865
-// against 873 / 864 us).
+// Sites of a band.  The work-groups in flight on an XCD cover ~32 000 sites: several layers of a
+// band, so most links that they load as z +- 1 neighbours are in the L2, but less than one whole
+// layer of 192 x 192.  Per step, whole layers against bands of at most 4096 / 6144 / 9216 sites:
+// 512 x 192 x 192 SU(3) FP32 2854 us against 2705 / 2703 / 2695, 256 x 192 x 192 SU(2) FP64 910
+// against 875 / 870 / 869, 128 x 150 x 150 SU(3) FP64 877 against 825 / 822 / 835; layers of up to
+// 9216 sites are as fast whole (1024 x 96 x 96 SU(2) FP64 865 against 873 / 864 us).
 constexpr int BAND_SITES = 9216;
 // block j of an XCD's slab of (at most) nk layers -> layer of the slab, block of the layer
 GL_HD void slab_order(const ColMap& m, uint32_t nk, uint32_t j, int& zl, uint32_t& ch) {

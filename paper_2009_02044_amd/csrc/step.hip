@@ -1,7 +1,7 @@
 // Leapfrog step with the CPIC charge hop (Sec. 3: eqs. lattice_1, lattice_2,
 // plaquette, continuity and the nearest-grid-point transport rule).
 //
-// One thread owns one site x and its three links.  It forms the force terms
+// One thread owns one site x and its three links (small lattices: one link).  It forms the force terms
 //   f_i = sum_{j != i} a_j^-2 P(U_{i,j}(x) + U_{i,-j}(x))
 // plaquette by plaquette (stencil.h: plaquette_forces; a forward plaquette serves
 // both of its directions), then for each direction updates
