@@ -75,6 +75,9 @@ template <typename G, typename T> struct ObsAcc {
         d += 0.5 * ((double)eo.c[k] + (double)en) * (double)p.c[k];
       }
       sl += d / (c.a[2] * ai);
+      // summed here: otherwise the products of this plane wait at the end of the step, with its links
+      // in registers (38 spilled; 512 x 64 x 64 SU(3) 814 -> 651 us)
+      asm volatile("" : "+v"(sl));
     }
   }
 };
