@@ -1336,11 +1336,10 @@ static int adjoint_reverse(glasma_ctx* c, void* work, size_t work_bytes, Seed&& 
         sc.hop = is_hop(c, sk + m) ? 1 : 0;
         sc.offA = sc.offB = off_at(c, s0, off0, sk + m);
         sc.scheme = 0;
-        sc.from_E = (const T*)x.E - (const T*)y.E;
-        sc.from_rho = (const T*)rho[m].rA - (const T*)y.rA;   // the same for rho_B
+        const StepFrom from{(const T*)x.E - (const T*)y.E, (const T*)rho[m].rA - (const T*)y.rA};   // rho_B as rho_A
         rho[m + 1] = sc.hop ? y : rho[m];
         const bool ru = c->p.reunit_every > 0 && (sk + m + 1) % c->p.reunit_every == 0;
-        launch_leapfrog<G, T>((const T*)x.U, (T*)y.U, (T*)y.E, (T*)y.rA, (T*)y.rB, c->g, sc, ru, c->stream);
+        launch_leapfrog<G, T>((const T*)x.U, (T*)y.U, (T*)y.E, (T*)y.rA, (T*)y.rB, c->g, sc, ru, c->stream, from);
       }
       for (int64_t m = len - 1; m >= 0; --m) {
         const int64_t s = sk + m;

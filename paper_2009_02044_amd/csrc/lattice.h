@@ -371,8 +371,10 @@ struct StepConst {
   int hop;           // 1 on a step where every charge advances one cell
   int offA, offB;    // co-moving storage offsets of the two charge populations
   int scheme;        // 0 leapfrog, 1 semi-implicit
-  // where a plain step reads the E and the charges that it writes: so many elements from there
-  int64_t from_E = 0, from_rho = 0;
+};
+// where a step reads the E and the charges that it writes: so many elements from there
+struct StepFrom {
+  int64_t E = 0, rho = 0;
 };
 
 // Co-moving charge storage: nucleus B (moving +z) keeps the charge that sits at

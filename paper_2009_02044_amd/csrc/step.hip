@@ -84,11 +84,15 @@ template <typename G, typename T> struct ObsAcc {
 
 // Update of link (x, i) from the force term f_i of plaquette_forces (F_i = -f_i / a_i);
 // the z-link thread also hops the charges.
-template <typename G, typename T, bool HOP, bool OBS = false>
+// FROM: the E and the charges of the state before are read from elsewhere (a step in place adds
+// no offsets: read through a second base, the SU(2) FP64 kernel holds 4 registers more and a wave
+// per SIMD less, 512 x 64 x 64 2.73 -> 2.80 ms for 16 steps).
+template <typename G, typename T, bool HOP, bool OBS = false, bool FROM = false>
 __device__ __forceinline__ void finish_link(const typename G::Link& Ui, const typename G::Alg& fi,
                                             T* __restrict__ Unew, T* __restrict__ E, T* __restrict__ rhoA,
                                             T* __restrict__ rhoB, const Geom& g, const StepConst& c, Site x,
-                                            uint32_t s, int i, bool reunit, ObsAcc<G, T>* oa = nullptr) {
+                                            uint32_t s, int i, bool reunit, ObsAcc<G, T>* oa = nullptr,
+                                            StepFrom from = {}) {
   using L = typename G::Link;
   using A = typename G::Alg;
   constexpr int NG = G::NG;
@@ -96,7 +100,7 @@ __device__ __forceinline__ void finish_link(const typename G::Link& Ui, const ty
   // i is a run-time value: select the spacing (no indexed local array)
   const double ai = i == 0 ? c.a[0] : (i == 1 ? c.a[1] : c.a[2]);
   A e;
-  load_alg_own(e, OBS ? E : E + c.from_E, i, s, Vp);
+  load_alg_own(e, FROM ? E + from.E : E, i, s, Vp);
   A eo;
   if constexpr (OBS) eo = e;
   const T kf = (T)(-c.dt / ai);
@@ -106,8 +110,8 @@ __device__ __forceinline__ void finish_link(const typename G::Link& Ui, const ty
     const uint32_t sB = site_index(g, x.x, x.y, slotB(x.z, c.offB, g.nz));
     const uint32_t sA = site_index(g, x.x, x.y, slotA(wrap_add(x.z, 1, g.nz), c.offA, g.nz));
     A rb, ra;
-    load_alg_own(rb, OBS ? rhoB : rhoB + c.from_rho, 0, sB, Vp);
-    load_alg_own(ra, OBS ? rhoA : rhoA + c.from_rho, 0, sA, Vp);
+    load_alg_own(rb, FROM ? rhoB + from.rho : rhoB, 0, sB, Vp);
+    load_alg_own(ra, FROM ? rhoA + from.rho : rhoA, 0, sA, Vp);
     A rbn = G::transport(Ui, rb);
     A ran = G::transport_inv(Ui, ra);
     store_alg(rbn, rhoB, 0, sB, Vp);
@@ -136,12 +140,12 @@ __device__ __forceinline__ void finish_link(const typename G::Link& Ui, const ty
 }
 
 // The whole site update from plaquette forces.
-template <typename G, typename T, bool HOP, bool XS, int OWN, bool OBS = false>
+template <typename G, typename T, bool HOP, bool XS, int OWN, bool OBS = false, bool FROM = false>
 __device__ __forceinline__ void update_site(const T* __restrict__ U, T* __restrict__ Unew, T* __restrict__ E,
                                             T* __restrict__ rhoA, T* __restrict__ rhoB, const Geom& g,
                                             const StepConst& c, const double* inv_a2, Site x, uint32_t s,
                                             bool reunit, typename Vec16<T>::type* slot, uint32_t TB,
-                                            ObsAcc<G, T>* oa = nullptr) {
+                                            ObsAcc<G, T>* oa = nullptr, StepFrom from = {}) {
   using L = typename G::Link;
   const GlobalLinks<T> fetch{U, g.Vp};
   const OwnLinks<G, T, OWN> own(fetch, s, slot, threadIdx.x, TB);
@@ -155,7 +159,7 @@ __device__ __forceinline__ void update_site(const T* __restrict__ U, T* __restri
     typename G::Alg fi;
 #pragma unroll
     for (int k = 0; k < G::NG; ++k) fi.c[k] = i == 0 ? f[0].c[k] : (i == 1 ? f[1].c[k] : f[2].c[k]);
-    finish_link<G, T, HOP, OBS>(Ui, fi, Unew, E, rhoA, rhoB, g, c, x, s, i, reunit, oa);
+    finish_link<G, T, HOP, OBS, FROM>(Ui, fi, Unew, E, rhoA, rhoB, g, c, x, s, i, reunit, oa, from);
   }
 }
 
@@ -180,18 +184,20 @@ template <typename G, typename T, int TB> struct OwnLds {
 // sums of this work-group (full work-groups only: every thread reaches the reduction).
 // The observing variant is held to two waves per SIMD (its traces live in LDS, below).
 // RU: the step also reunitarises the new links (in double arithmetic, before the store).
-template <typename G, typename T, bool HOP, bool XS, bool OBS = false, bool RU = false>
+template <typename G, typename T, bool HOP, bool XS, bool OBS = false, bool RU = false, bool FROM = false>
 __global__ void __launch_bounds__(LF_BS, OBS ? 2 : GL_LF_WAVES) k_leapfrog(const T* __restrict__ U, T* __restrict__ Unew,
                                                                  T* __restrict__ E, T* __restrict__ rhoA,
                                                                  T* __restrict__ rhoB, Geom g, StepConst c,
-                                                                 ColMap m, double* __restrict__ partial = nullptr) {
+                                                                 ColMap m, double* __restrict__ partial,
+                                                                 StepFrom from) {
   Site x;
   uint32_t s;
   __shared__ typename Vec16<T>::type slot[OwnLds<G, T, LF_BS>::N];
   if (!col_map_site(g, m, blockIdx.x, threadIdx.x, LF_BS, x, s)) return;
   const double inv_a2[3] = {1.0 / (c.a[0] * c.a[0]), 1.0 / (c.a[1] * c.a[1]), 1.0 / (c.a[2] * c.a[2])};
   if constexpr (!OBS) {
-    update_site<G, T, HOP, XS, OwnMode<G, T>::value>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s, RU, slot, LF_BS);
+    update_site<G, T, HOP, XS, OwnMode<G, T>::value, false, FROM>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s, RU, slot,
+                                                                  LF_BS, nullptr, from);
   } else {
     __shared__ double trs[3 * LF_BS];
     ObsAcc<G, T> oa;
@@ -231,27 +237,29 @@ __global__ void __launch_bounds__(LF_BS, OBS ? 2 : GL_LF_WAVES) k_leapfrog(const
 // site's.  Each link's force comes out of the same operations in the same order as the site
 // kernel's, so the state does not depend on which of the two runs (bitwise).
 constexpr int LF_LINK_BS = 64;
-template <typename G, typename T, bool HOP, bool XS, bool RU, int D>
+template <typename G, typename T, bool HOP, bool XS, bool RU, bool FROM, int D>
 __device__ __forceinline__ void update_link(const T* __restrict__ U, T* __restrict__ Unew, T* __restrict__ E,
                                             T* __restrict__ rhoA, T* __restrict__ rhoB, const Geom& g,
-                                            const StepConst& c, const double* inv_a2, Site x, uint32_t s) {
+                                            const StepConst& c, const double* inv_a2, Site x, uint32_t s,
+                                            StepFrom from) {
   const GlobalLinks<T> fetch{U, g.Vp};
   const OwnLinks<G, T, OWN_REGS> own(fetch, s, nullptr, 0, 0);
   typename G::Alg f[3];
   plaquette_forces<G, XS, false, 1 << D>(fetch, own, g, x, inv_a2, f);
-  finish_link<G, T, HOP>(own.O[D], f[D], Unew, E, rhoA, rhoB, g, c, x, s, D, RU);
+  finish_link<G, T, HOP, false, FROM>(own.O[D], f[D], Unew, E, rhoA, rhoB, g, c, x, s, D, RU, nullptr, from);
 }
-template <typename G, typename T, bool HOP, bool XS, bool RU>
+template <typename G, typename T, bool HOP, bool XS, bool RU, bool FROM>
 __global__ void __launch_bounds__(LF_LINK_BS) k_leapfrog_link(const T* __restrict__ U, T* __restrict__ Unew,
                                                               T* __restrict__ E, T* __restrict__ rhoA,
-                                                              T* __restrict__ rhoB, Geom g, StepConst c, ColMap m) {
+                                                              T* __restrict__ rhoB, Geom g, StepConst c, ColMap m,
+                                                              StepFrom from) {
   Site x;
   uint32_t s;
   if (!col_map_site(g, m, blockIdx.x, threadIdx.x, LF_LINK_BS, x, s)) return;
   const double inv_a2[3] = {1.0 / (c.a[0] * c.a[0]), 1.0 / (c.a[1] * c.a[1]), 1.0 / (c.a[2] * c.a[2])};
-  if (blockIdx.y == 0) update_link<G, T, false, XS, RU, 0>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s);
-  else if (blockIdx.y == 1) update_link<G, T, false, XS, RU, 1>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s);
-  else update_link<G, T, HOP, XS, RU, 2>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s);
+  if (blockIdx.y == 0) update_link<G, T, false, XS, RU, FROM, 0>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s, from);
+  else if (blockIdx.y == 1) update_link<G, T, false, XS, RU, FROM, 1>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s, from);
+  else update_link<G, T, HOP, XS, RU, FROM, 2>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s, from);
 }
 
 // Sites up to which a thread per link is taken: where the two kernels take the same time.  Per
@@ -263,30 +271,36 @@ template <typename G, typename T> constexpr int64_t LF_LINK_MAX = G::NC == 3 && 
 
 template <typename G, typename T>
 void launch_leapfrog(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const Geom& g, const StepConst& c,
-                     bool reunit, hipStream_t st) {
+                     bool reunit, hipStream_t st, StepFrom from) {
   // rows inside wavefronts: x neighbours from other lanes
   const bool xs = rows_in_wavefronts(g.nt);
   const bool link = g.V <= LF_LINK_MAX<G, T>;
   const int bs = link ? LF_LINK_BS : LF_BS;
   const ColMap m = col_map(g, bs);
   const dim3 grid(col_map_blocks(g, m), link ? 3 : 1);
-  auto pick = [&](auto hop, auto xn, auto ru) {
-    constexpr bool H = decltype(hop)::value, X = decltype(xn)::value, R = decltype(ru)::value;
+  auto pick = [&](auto hop, auto xn, auto ru, auto fr) {
+    constexpr bool H = decltype(hop)::value, X = decltype(xn)::value, R = decltype(ru)::value,
+                   F = decltype(fr)::value;
     if (link)
-      hipLaunchKernelGGL((k_leapfrog_link<G, T, H, X, R>), grid, dim3(bs), 0, st, U, Unew, E, rhoA, rhoB, g, c, m);
+      hipLaunchKernelGGL((k_leapfrog_link<G, T, H, X, R, F>), grid, dim3(bs), 0, st, U, Unew, E, rhoA, rhoB, g, c, m,
+                         from);
     else
-      hipLaunchKernelGGL((k_leapfrog<G, T, H, X, false, R>), grid, dim3(bs), 0, st, U, Unew, E, rhoA, rhoB, g, c, m,
-                         nullptr);
+      hipLaunchKernelGGL((k_leapfrog<G, T, H, X, false, R, F>), grid, dim3(bs), 0, st, U, Unew, E, rhoA, rhoB, g, c,
+                         m, nullptr, from);
   };
   using Y = std::true_type;
   using N = std::false_type;
-  if (!reunit) {
-    if (c.hop) xs ? pick(Y{}, Y{}, N{}) : pick(Y{}, N{}, N{});
-    else xs ? pick(N{}, Y{}, N{}) : pick(N{}, N{}, N{});
-  } else {
-    if (c.hop) xs ? pick(Y{}, Y{}, Y{}) : pick(Y{}, N{}, Y{});
-    else xs ? pick(N{}, Y{}, Y{}) : pick(N{}, N{}, Y{});
-  }
+  auto with = [&](auto fr) {
+    if (!reunit) {
+      if (c.hop) xs ? pick(Y{}, Y{}, N{}, fr) : pick(Y{}, N{}, N{}, fr);
+      else xs ? pick(N{}, Y{}, N{}, fr) : pick(N{}, N{}, N{}, fr);
+    } else {
+      if (c.hop) xs ? pick(Y{}, Y{}, Y{}, fr) : pick(Y{}, N{}, Y{}, fr);
+      else xs ? pick(N{}, Y{}, Y{}, fr) : pick(N{}, N{}, Y{}, fr);
+    }
+  };
+  if (from.E == 0 && from.rho == 0) with(N{});
+  else with(Y{});
 }
 
 // The observing step: the leapfrog step that also writes the energy slots of the
@@ -302,14 +316,14 @@ void launch_leapfrog_observe(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const 
   const bool xs = rows_in_wavefronts(g.nt);
   if (c.hop) {
     if (xs) hipLaunchKernelGGL((k_leapfrog<G, T, true, true, true>), dim3(nbc), dim3(bs), 0, st, U, Unew, E, rhoA,
-                               rhoB, g, c, m, partial);
+                               rhoB, g, c, m, partial, StepFrom{});
     else hipLaunchKernelGGL((k_leapfrog<G, T, true, false, true>), dim3(nbc), dim3(bs), 0, st, U, Unew, E, rhoA,
-                            rhoB, g, c, m, partial);
+                            rhoB, g, c, m, partial, StepFrom{});
   } else {
     if (xs) hipLaunchKernelGGL((k_leapfrog<G, T, false, true, true>), dim3(nbc), dim3(bs), 0, st, U, Unew, E, rhoA,
-                               rhoB, g, c, m, partial);
+                               rhoB, g, c, m, partial, StepFrom{});
     else hipLaunchKernelGGL((k_leapfrog<G, T, false, false, true>), dim3(nbc), dim3(bs), 0, st, U, Unew, E, rhoA,
-                            rhoB, g, c, m, partial);
+                            rhoB, g, c, m, partial, StepFrom{});
   }
 }
 template void launch_leapfrog_observe<Su3<double>, double>(const double*, double*, double*, double*, double*,
@@ -431,9 +445,9 @@ template void launch_batch_step<Su3<double>, double>(char*, const EventDesc*, co
 template void launch_batch_step<Su2<float>, float>(char*, const EventDesc*, const uint32_t*, const BatchConst&, const int64_t*, int, int, hipStream_t);
 template void launch_batch_step<Su3<float>, float>(char*, const EventDesc*, const uint32_t*, const BatchConst&, const int64_t*, int, int, hipStream_t);
 
-template void launch_leapfrog<Su2<double>, double>(const double*, double*, double*, double*, double*, const Geom&, const StepConst&, bool, hipStream_t);
-template void launch_leapfrog<Su3<double>, double>(const double*, double*, double*, double*, double*, const Geom&, const StepConst&, bool, hipStream_t);
-template void launch_leapfrog<Su2<float>, float>(const float*, float*, float*, float*, float*, const Geom&, const StepConst&, bool, hipStream_t);
-template void launch_leapfrog<Su3<float>, float>(const float*, float*, float*, float*, float*, const Geom&, const StepConst&, bool, hipStream_t);
+template void launch_leapfrog<Su2<double>, double>(const double*, double*, double*, double*, double*, const Geom&, const StepConst&, bool, hipStream_t, StepFrom);
+template void launch_leapfrog<Su3<double>, double>(const double*, double*, double*, double*, double*, const Geom&, const StepConst&, bool, hipStream_t, StepFrom);
+template void launch_leapfrog<Su2<float>, float>(const float*, float*, float*, float*, float*, const Geom&, const StepConst&, bool, hipStream_t, StepFrom);
+template void launch_leapfrog<Su3<float>, float>(const float*, float*, float*, float*, float*, const Geom&, const StepConst&, bool, hipStream_t, StepFrom);
 
 }  // namespace gl
