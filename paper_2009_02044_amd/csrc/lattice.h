@@ -280,78 +280,95 @@ template <uint32_t C> GL_HD uint32_t xcd_chunk_remap(uint32_t b, uint32_t nb) {
 #ifndef GL_ZSLAB
 #define GL_ZSLAB 1
 #endif
+// Division by a number known on the host: q = n m >> s, exact for n < 2^29 (m = ceil(2^s / d), s =
+// 30 + ceil(log2 d): the excess n (m d - 2^s) / d is below 2^(s-1) / d).  On uniform values
+// three scalar instructions; the compiler's own division is about twenty in a row, which the
+// waves of a short kernel wait for before their first load.
+struct Div {
+  uint32_t m, s;
+};
+inline Div div_by(int64_t d) {
+  Div r;
+  r.s = 30;
+  while (((int64_t)1 << (r.s - 30)) < d) ++r.s;
+  r.m = (uint32_t)((((uint64_t)1 << r.s) + (uint64_t)d - 1) / (uint64_t)d);
+  return r;
+}
+GL_HD uint32_t quot(uint32_t n, Div d) { return (uint32_t)(((uint64_t)n * d.m) >> d.s); }
+
 struct ColMap {
   int r0, rem;   // rows (rows) or layers (slabs) per XCD: r0 + (k < rem)
   int bt;        // blocks per (XCD, layer) (rows) or per layer (slabs)
   int slab;      // 1: slab decomposition
-  int band;      // slabs: blocks per band, a band swept through the slab before the next
+  int band;      // blocks per band, a band swept through the slab before the next (rows: one band)
+  int nk;        // layers that an XCD sweeps (slabs: the longest slab)
+  int last;      // blocks of the last band
+  Div by_sweep, by_band, by_last;   // by nk band, band, last
 };
-// Sites of a band.  The work-groups in flight on an XCD cover ~32 000 sites: several layers of a
-// band, so most links that they load as z +- 1 neighbours are in the L2, but less than one whole
-// layer of 192 x 192.  Per step, whole layers against bands of at most 4096 / 6144 / 9216 sites:
+// Sites of a band.  Per step, whole layers against bands of at most 4096 / 6144 / 9216 sites:
 // 512 x 192 x 192 SU(3) FP32 2854 us against 2705 / 2703 / 2695, 256 x 192 x 192 SU(2) FP64 910
-// against 875 / 870 / 869, 128 x 150 x 150 SU(3) FP64 877 against 825 / 822 / 835; layers of up to
-// 9216 sites are as fast whole (1024 x 96 x 96 SU(2) FP64 865 against 873 / 864 us).
+// against 875 / 870 / 869, 128 x 150 x 150 SU(3) FP64 877 against 825 / 822 / 835.
 constexpr int BAND_SITES = 9216;
-// block j of an XCD's slab of (at most) nk layers -> layer of the slab, block of the layer
-GL_HD void slab_order(const ColMap& m, uint32_t nk, uint32_t j, int& zl, uint32_t& ch) {
-  const uint32_t c0 = j / (nk * (uint32_t)m.band) * (uint32_t)m.band;
-  const uint32_t w = (uint32_t)m.bt - c0 < (uint32_t)m.band ? (uint32_t)m.bt - c0 : (uint32_t)m.band;
-  const uint32_t r = j - c0 * nk;
-  zl = (int)(r / w);
-  ch = c0 + r % w;
+// block j of an XCD -> layer of its range, block of the layer
+GL_HD void sweep_order(const ColMap& m, uint32_t j, int& zl, uint32_t& ch) {
+  const uint32_t c0 = quot(j, m.by_sweep) * (uint32_t)m.band;
+  const bool end = c0 + (uint32_t)m.band >= (uint32_t)m.bt;
+  const uint32_t r = j - c0 * (uint32_t)m.nk;
+  const uint32_t q = quot(r, Div{end ? m.by_last.m : m.by_band.m, end ? m.by_last.s : m.by_band.s});
+  zl = (int)q;
+  ch = c0 + r - q * (uint32_t)(end ? m.last : m.band);
 }
-inline ColMap col_map(const Geom& g, int bs, int slab = GL_ZSLAB) {
+// whole: layers (slabs) of up to so many sites are swept whole
+inline ColMap col_map(const Geom& g, int bs, int64_t whole = BAND_SITES, int slab = GL_ZSLAB) {
   ColMap m;
   m.slab = slab;
   const int n = slab ? g.nz : g.nt;
   m.r0 = n / NXCD;
   m.rem = n % NXCD;
-  const int64_t seg = slab ? (int64_t)g.layer : (int64_t)(m.r0 + (m.rem > 0 ? 1 : 0)) * g.nt;
+  const int most = m.r0 + (m.rem > 0 ? 1 : 0);
+  const int64_t seg = slab ? (int64_t)g.layer : (int64_t)most * g.nt;
   m.bt = (int)((seg + bs - 1) / bs);
-  const int nb = (int)((seg + BAND_SITES - 1) / BAND_SITES);   // bands of equal size
+  const int nb = slab && seg > whole ? (int)((seg + BAND_SITES - 1) / BAND_SITES) : 1;   // bands of equal size
   m.band = (m.bt + nb - 1) / nb;
+  m.last = m.bt - (m.bt - 1) / m.band * m.band;
+  m.nk = slab ? most : g.nz;
+  m.by_sweep = div_by((int64_t)m.nk * m.band);
+  m.by_band = div_by(m.band);
+  m.by_last = div_by(m.last);
   return m;
 }
-inline uint32_t col_map_blocks(const Geom& g, const ColMap& m) {
-  const int64_t per = m.slab ? (int64_t)(m.r0 + (m.rem > 0 ? 1 : 0)) : (int64_t)g.nz;
-  return (uint32_t)(NXCD * per * m.bt);
+inline uint32_t col_map_blocks(const Geom&, const ColMap& m) {
+  return (uint32_t)(NXCD * (int64_t)m.nk * m.bt);
 }
 // partial-sum slots per layer: one per block that covers sites of that layer
 GL_HD int col_map_slots_per_layer(const ColMap& m) { return m.slab ? m.bt : NXCD * m.bt; }
 // layer of block b (may be >= nz or past the XCD's slab for idle blocks) and its slot
 GL_HD void col_map_block(const ColMap& m, uint32_t b, int& z, uint32_t& slot) {
   const int k = (int)(b % NXCD);
-  const uint32_t j = b / NXCD;
-  uint32_t ch = j % (uint32_t)m.bt;
+  int zl;
+  uint32_t ch;
+  sweep_order(m, b / NXCD, zl, ch);
   if (m.slab) {
-    int zl;
-    slab_order(m, (uint32_t)(m.r0 + (m.rem > 0 ? 1 : 0)), j, zl, ch);
     const int nk = m.r0 + (k < m.rem ? 1 : 0);
     z = zl < nk ? k * m.r0 + (k < m.rem ? k : m.rem) + zl : 0x7fffffff;
     slot = ch;
   } else {
-    z = (int)(j / (uint32_t)m.bt);
+    z = zl;
     slot = (uint32_t)k * m.bt + ch;
   }
 }
 // site of thread t in block b, or false when the thread has no site
 GL_HD bool col_map_site(const Geom& g, const ColMap& m, uint32_t b, uint32_t t, uint32_t bs, Site& x, uint32_t& s) {
   const int k = (int)(b % NXCD);
-  const uint32_t j = b / NXCD;
-  uint32_t ch = j % (uint32_t)m.bt;
   int z, y0;
-  uint32_t seg;
+  uint32_t ch, seg;
+  sweep_order(m, b / NXCD, z, ch);
   if (m.slab) {
-    int zl;
-    slab_order(m, (uint32_t)(m.r0 + (m.rem > 0 ? 1 : 0)), j, zl, ch);
-    const int nk = m.r0 + (k < m.rem ? 1 : 0);
-    if (zl >= nk) return false;
-    z = k * m.r0 + (k < m.rem ? k : m.rem) + zl;
+    if (z >= m.r0 + (k < m.rem ? 1 : 0)) return false;
+    z += k * m.r0 + (k < m.rem ? k : m.rem);
     y0 = 0;
     seg = (uint32_t)g.layer;
   } else {
-    z = (int)(j / (uint32_t)m.bt);
     y0 = k * m.r0 + (k < m.rem ? k : m.rem);
     seg = (uint32_t)(m.r0 + (k < m.rem ? 1 : 0)) * (uint32_t)g.nt;
   }

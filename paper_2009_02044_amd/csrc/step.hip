@@ -269,6 +269,15 @@ __global__ void __launch_bounds__(LF_LINK_BS) k_leapfrog_link(const T* __restric
 // 8.1-23.1 / 8.5-24.5 us.  (SU(3) in double precision takes the registers of a whole SIMD lane.)
 template <typename G, typename T> constexpr int64_t LF_LINK_MAX = G::NC == 3 && sizeof(T) == 8 ? 40960 : 81920;
 
+// Sites of a layer up to which it is swept whole: half of what the work-groups in flight on an XCD
+// cover (32 CUs, 4 SIMDs, 64 sites a wave), which is 2, 4, 4 and 8 waves per SIMD for SU(3) FP64,
+// SU(3) FP32, SU(2) FP64 and SU(2) FP32.  16 steps, whole against bands: SU(3) FP64 64 x 97 x 97 3169 /
+// 3042 us, 128 x 128 x 128 10116 / 9646; SU(3) FP32 32 x 128 x 128 1289 / 1311, 128 x 150 x 150 7051 /
+// 6893; SU(2) FP64 64 x 100 x 100 1027 / 1047, 32 x 128 x 128 853 / 867, 128 x 150 x 150 4730 / 4552; SU(2)
+// FP32 128 x 150 x 150 2441 / 2481, 40 x 192 x 192 990 / 896.
+template <typename G, typename T>
+constexpr int64_t WHOLE_LAYER = sizeof(T) == 8 ? (G::NC == 3 ? 9216 : 16384) : (G::NC == 3 ? 16384 : 32768);
+
 template <typename G, typename T>
 void launch_leapfrog(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const Geom& g, const StepConst& c,
                      bool reunit, hipStream_t st, StepFrom from) {
@@ -276,7 +285,7 @@ void launch_leapfrog(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const Geom& g,
   const bool xs = rows_in_wavefronts(g.nt);
   const bool link = g.V <= LF_LINK_MAX<G, T>;
   const int bs = link ? LF_LINK_BS : LF_BS;
-  const ColMap m = col_map(g, bs);
+  const ColMap m = col_map(g, bs, WHOLE_LAYER<G, T>);
   const dim3 grid(col_map_blocks(g, m), link ? 3 : 1);
   auto pick = [&](auto hop, auto xn, auto ru, auto fr) {
     constexpr bool H = decltype(hop)::value, X = decltype(xn)::value, R = decltype(ru)::value,
@@ -311,7 +320,7 @@ template <typename G, typename T>
 void launch_leapfrog_observe(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const Geom& g, const StepConst& c,
                              double* partial, hipStream_t st) {
   const int bs = LF_BS;
-  const ColMap m = col_map(g, bs);
+  const ColMap m = col_map(g, bs, WHOLE_LAYER<G, T>);
   const unsigned nbc = col_map_blocks(g, m);
   const bool xs = rows_in_wavefronts(g.nt);
   if (c.hop) {

@@ -643,3 +643,43 @@ def test_observables_over_partial_sums(nz, nt):
     for k in ("gauss_l2", "rho_l2", "gauss_max"):
         if k in oo:
             assert abs(go[k] - oo[k]) <= 1e-11 * abs(oo[k]) + 1e-14, k
+
+
+def _tiled_pair(pkg, nc, fp, nz, nt, reps, seed):
+    """A lattice of nz layers and one of the same layers repeated `reps` times along z."""
+    w = synth.Workload(f"su{nc}-{nz}x{nt}", nc=nc, nz=nz, nt=nt, mu=0.5, sigma=0.8, seed=seed)
+    print("case:", w.name, "fp", fp, "x", reps, flush=True)
+    p, mv = mv_setup(w)
+    rA, rB = synth.mv_charges(w.seed, nc, nt, w.mu, w.a_T)
+    st, _ = init_mv.initial_state(rA, rB, nz, p, mv)
+    arrs = to_comp(st)
+    kw = dict(nc=nc, nt=nt, a_T=w.a_T, a_L=w.a_L, dt=w.dt, fp=fp, reunit_every=4 if fp == 32 else 0)
+    one, many = pkg.Lattice(nz=nz, **kw), pkg.Lattice(nz=nz * reps, **kw)
+    one.init_state(*arrs, step0=0)
+    many.init_state(*[np.tile(x, reps) for x in arrs], step0=0)
+    return one, many
+
+
+def _same_layers(one, many, reps):
+    a, b = one.get_state(), many.get_state()
+    for k in ("U", "E", "rhoA", "rhoB"):
+        x = b[k].reshape(*b[k].shape[:-1], reps, one.V)
+        assert np.array_equal(x, np.broadcast_to(a[k][..., None, :], x.shape)), k
+
+
+@pytest.mark.parametrize("nc,fp,nt", [(3, 64, 150), (2, 64, 150), (3, 32, 150), (2, 32, 192), (3, 64, 128), (2, 64, 192)])
+def test_bands_of_several_layers(nc, fp, nt):
+    """Large layers in bands with two and three layers per XCD (the last band narrower at nt = 150:
+    work-groups in 30, 30, 28) against three layers, one per XCD, which need no order: steps
+    with and without a hop and an observing step (fused for FP64 at nt = 128, 192): state and
+    slices bitwise, an observing step's slots being those of the layer."""
+    pkg = lattice_or_skip()
+    nz, reps = 3, 6
+    one, many = _tiled_pair(pkg, nc, fp, nz, nt, reps, 450 + nt)
+    for lat in (one, many):
+        lat.buf = lat.obs_buffer()
+        lat.step_observe(4, lat.buf)
+    a = pkg.Lattice.unpack_obs(one.buf, nz)["tmunu_z"]
+    b = pkg.Lattice.unpack_obs(many.buf, nz * reps)["tmunu_z"]
+    assert np.array_equal(b, np.tile(a, reps))
+    _same_layers(one, many, reps)
