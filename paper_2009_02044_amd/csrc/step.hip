@@ -262,12 +262,32 @@ __global__ void __launch_bounds__(LF_LINK_BS) k_leapfrog_link(const T* __restric
   else update_link<G, T, HOP, XS, RU, FROM, 2>(U, Unew, E, rhoA, rhoB, g, c, inv_a2, x, s, from);
 }
 
-// Sites up to which a thread per link is taken: where the two kernels take the same time.  Per
-// step, site against link kernel: 64 x 8 x 8 SU(2) FP64 6.3 / 3.9 us, SU(3) FP64 13.7 / 7.2 us, FP32
-// 12.3 / 6.4 us; 75 x 21 x 21 SU(3) FP64 18.3 / 16.3 us, FP32 15.4 / 9.5 us; SU(3) FP64 36 864 sites
-// 18.7 / 17.2 us, 49 152 20.9 / 23.0 us; the others 81 920 sites 7.5-19.4 / 6.6-18.2 us, 114 688
-// 8.1-23.1 / 8.5-24.5 us.  (SU(3) in double precision takes the registers of a whole SIMD lane.)
-template <typename G, typename T> constexpr int64_t LF_LINK_MAX = G::NC == 3 && sizeof(T) == 8 ? 40960 : 81920;
+// Whether a step takes a thread per link.  Both kernels take as long as the XCD with the most layers,
+// so the rule counts there: the waves of the link kernel, and for SU(3) FP64 the work-groups of the
+// site kernel, which runs one per CU as long as there are 32 of them (0.30 ms for 16 steps) and a second
+// one beside it above (0.51 - 0.64 ms); its link kernel runs one wave per SIMD (1.0 us more for every
+// wave of the XCD).  With rows inside wavefronts (nt = 16, 32, 64) the site kernel is the cheaper for it.
+// 16 steps, site against link kernel (us):
+//   SU(3) FP64: 252 waves 295 / 277, 324 waves 309 / 366, 384 waves 332 / 391; above 32 work-groups:
+//     375 waves 508 / 389, 480 waves 541 / 519, 540 waves 559 / 585
+//   SU(2) FP64: 540 waves 165 / 167, 621 waves 190 / 152, 672 waves 198 / 225; rows inside: 576 waves 184 /
+//     175, 624 waves 176 / 182
+//   SU(3) FP32: 618 waves 334 / 319, 621 waves 399 / 299, 672 waves 342 / 368; inside: 576 waves 314 / 289,
+//     624 waves 315 / 330
+//   SU(2) FP32: 672 waves 143 / 123, 864 waves 175 / 140; inside: 624 waves 116 / 111, 672 waves 116 / 121
+// (64 x 8 x 8, in this order: 219 / 114, 97 / 59, 195 / 102, 87 / 65.)
+// Layers of at most 64 sites leave three of a site work-group's four waves without work: 1250 x 8 x 8
+// 746 / 533, 150 / 145, 427 / 280, 111 / 95 (measured up to 80 000 sites).
+constexpr int64_t LF_LINK_SMALL = 81920;
+template <typename G, typename T> bool step_by_links(const Geom& g) {
+  if (g.layer <= LF_LINK_BS && g.V <= LF_LINK_SMALL) return true;
+  const int64_t waves = 3 * (int64_t)(col_map_blocks(g, col_map(g, LF_LINK_BS)) / NXCD);
+  const bool inside = rows_in_wavefronts(g.nt);
+  if (G::NC == 3 && sizeof(T) == 8)
+    return waves <= (col_map_blocks(g, col_map(g, LF_BS)) / NXCD <= 32 ? 256 : 512);
+  if (G::NC == 2 && sizeof(T) == 4) return waves <= (inside ? 640 : 864);
+  return waves <= (inside ? 600 : 640);
+}
 
 // Sites of a layer up to which it is swept whole: half of what the work-groups in flight on an XCD
 // cover (32 CUs, 4 SIMDs, 64 sites a wave), which is 2, 4, 4 and 8 waves per SIMD for SU(3) FP64,
@@ -283,7 +303,7 @@ void launch_leapfrog(const T* U, T* Unew, T* E, T* rhoA, T* rhoB, const Geom& g,
                      bool reunit, hipStream_t st, StepFrom from) {
   // rows inside wavefronts: x neighbours from other lanes
   const bool xs = rows_in_wavefronts(g.nt);
-  const bool link = g.V <= LF_LINK_MAX<G, T>;
+  const bool link = step_by_links<G, T>(g);
   const int bs = link ? LF_LINK_BS : LF_BS;
   const ColMap m = col_map(g, bs, WHOLE_LAYER<G, T>);
   const dim3 grid(col_map_blocks(g, m), link ? 3 : 1);

@@ -683,3 +683,19 @@ def test_bands_of_several_layers(nc, fp, nt):
     b = pkg.Lattice.unpack_obs(many.buf, nz * reps)["tmunu_z"]
     assert np.array_equal(b, np.tile(a, reps))
     _same_layers(one, many, reps)
+
+
+@pytest.mark.parametrize("nc,fp,nz,nt,sites", [(2, 64, 4, 16, 300000), (2, 32, 4, 21, 300000), (3, 64, 3, 8, 100000),
+                                               (3, 32, 4, 16, 200000), (3, 64, 5, 21, 100000), (2, 32, 2, 48, 200000),
+                                               (3, 64, 2, 48, 39168), (3, 32, 3, 9, 120000)])
+def test_link_step_at_its_limits(nc, fp, nz, nt, sites):
+    """A step by links (few layers) against a step by sites (the same layers repeated until more waves
+    per XCD than any limit of the rule): both kinds of rows, layers of one wave (8), sizes that
+    the number of sites alone does not decide (39 168 sites in 17 layers); bitwise, hops and no-hop
+    steps, FP32 with reunitarising steps."""
+    pkg = lattice_or_skip()
+    reps = sites // (nz * nt * nt) + 1
+    one, many = _tiled_pair(pkg, nc, fp, nz, nt, reps, 470 + nt)
+    one.step(6)
+    many.step(6)
+    _same_layers(one, many, reps)
