@@ -41,11 +41,11 @@ size_t observe_partial_doubles(const Geom& g) {
 // the projections and traces in registers held the pass at one wave per SIMD.  HAS_EN is a
 // template parameter: a run-time choice between the two sources of E(t + dt/2) made the
 // compiler spill several hundred registers (a 3x slower pass).
-// The empty asm on the sum keeps the compiler from moving a plane's products, of which only the sum
-// needs the projection, to the end of the pass, its links held in registers until there (spills
+// PIN: the empty asm on the sum keeps the compiler from moving a plane's products, of which only the
+// sum needs the projection, to the end of the pass, its links held in registers until there (spills
 // SU(3) FP64 48-108 -> 0-14, FP32 24-82 -> 0): 512 x 64 x 64 FP64 of a semi-implicit step 850 ->
-// 538 us, 384 x 48 x 48 FP32 306 -> 274 us.
-template <typename G, typename T, bool HAS_EN> struct PassObs {
+// 538 us, 384 x 48 x 48 FP32 306 -> 274 us.  pin_sums says where.
+template <typename G, typename T, bool HAS_EN, bool PIN> struct PassObs {
   static constexpr bool UNITARY = sizeof(T) == 4;   // links projected as they are read
   const T* E;
   const T* En;
@@ -72,7 +72,7 @@ template <typename G, typename T, bool HAS_EN> struct PassObs {
         d += 0.5 * (eo.c[k] + en) * p.c[k];
       }
       sl += d / (c.a[2] * ai);
-      asm volatile("" : "+v"(sl));   // summed here
+      if constexpr (PIN) asm volatile("" : "+v"(sl));   // summed here
     }
   }
 };
@@ -171,7 +171,7 @@ template <typename G, typename T> struct ProjLinks {
   }
 };
 
-template <typename G, typename T, bool XS, bool HAS_EN>
+template <typename G, typename T, bool XS, bool HAS_EN, bool PIN>
 __global__ void __launch_bounds__(OBS_BS, 2) k_observe(const T* __restrict__ U, const T* __restrict__ E,
                                                     const T* __restrict__ rhoA, const T* __restrict__ rhoB,
                                                     const T* __restrict__ En, Geom g, StepConst c,
@@ -208,7 +208,7 @@ __global__ void __launch_bounds__(OBS_BS, 2) k_observe(const T* __restrict__ U, 
       else return Own(fetch, s, (typename Vec16<T>::type*)slot_mem, threadIdx.x, OBS_BS);
     }();
     A f[3];
-    PassObs<G, T, HAS_EN> ob;
+    PassObs<G, T, HAS_EN, PIN> ob;
     ob.E = E;
     ob.En = En;
     ob.s = s;
@@ -451,8 +451,22 @@ void launch_observe(const T* U, const T* E, const T* rhoA, const T* rhoB, const 
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(nbx, g.nz), dim3(OBS_BS), 0, st, U, E, rhoA, rhoB, En, g, c, partial);
   };
-  if (rows_in_wavefronts(g.nt)) En ? go(k_observe<Gd, T, true, true>) : go(k_observe<Gd, T, true, false>);
-  else En ? go(k_observe<Gd, T, false, true>) : go(k_observe<Gd, T, false, false>);
+  const bool xs = rows_in_wavefronts(g.nt);
+  auto pick = [&](auto pin) {
+    constexpr bool P = decltype(pin)::value;
+    if (xs) En ? go(k_observe<Gd, T, true, true, P>) : go(k_observe<Gd, T, true, false, P>);
+    else En ? go(k_observe<Gd, T, false, true, P>) : go(k_observe<Gd, T, false, false, P>);
+  };
+  // SU(2) FP64 spills nothing either way: pinned it takes 122 registers for 144 and a fourth wave per
+  // SIMD, but waits for each plane's loads: 200 x 40 x 40 47.9 us pinned, 42.8 us not, 512 x 96 x 96 521 /
+  // 462, with rows in wavefronts 128 x 64 x 64 47.9 / 46.4 and, where the chip stays full longest, 512 x
+  // 64 x 64 164 / 174; with E(t + dt/2) read, 256 x 64 x 64 101 / 84.  (SU(2) FP32 takes the same time.)
+  if constexpr (G::NC == 2 && sizeof(T) == 8) {
+    if (xs && !En && g.V >= (1 << 20)) pick(std::true_type{});
+    else pick(std::false_type{});
+  } else {
+    pick(std::true_type{});
+  }
   launch_observe_finish(partial, nbx, g, c, out, st);
 }
 

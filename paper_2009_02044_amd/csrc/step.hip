@@ -75,9 +75,10 @@ template <typename G, typename T> struct ObsAcc {
         d += 0.5 * ((double)eo.c[k] + (double)en) * (double)p.c[k];
       }
       sl += d / (c.a[2] * ai);
-      // summed here: otherwise the products of this plane wait at the end of the step, with its links
-      // in registers (38 spilled; 512 x 64 x 64 SU(3) 814 -> 651 us)
-      asm volatile("" : "+v"(sl));
+      // SU(3): summed here, otherwise the products of this plane wait at the end of the step, with its
+      // links in registers (38 spilled; 512 x 64 x 64 814 -> 651 us).  SU(2) spills nothing without:
+      // 256 x 128 x 128 608 us with, 587 us without.
+      if constexpr (G::NC == 3) asm volatile("" : "+v"(sl));
     }
   }
 };
