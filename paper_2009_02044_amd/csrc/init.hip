@@ -51,7 +51,10 @@ size_t ic_work_doubles(const Geom& g, int ng) { return (size_t)6 * 2 * ng * g.la
 // and all nt columns were formed: 284 us a pass on 16 planes of 192 x 192 (18-20 us on
 // 64 x 64), now 14-28 us (5-10 us).  The table alone, without staging, took 45-76 us: each
 // term waited for its load.
-constexpr int DFT_BS = 256, DFT_LINES = 4, DFT_CHUNK = 256, DFT_FETCH = 8;
+// Sums are formed in blocks of DFT_BLOCK terms: a rounding then weighs a block's sum, not the whole
+// line's.  With half a spectrum the errors of +-k no longer cancel, and plain sums have phi 2-5% further
+// off than the full transform (9.0e-16 against 8.6e-16 of phi at nt = 192); in blocks 4.1e-16.
+constexpr int DFT_BS = 256, DFT_LINES = 4, DFT_CHUNK = 256, DFT_FETCH = 8, DFT_BLOCK = 16;
 constexpr int DFT_TABLE_MAX = 2048;   // 32 KB of LDS; longer lines evaluate each phase
 struct DftConst {
   int nt, h, nb;
@@ -116,26 +119,39 @@ k_dft(const double* __restrict__ in, double* __restrict__ out, DftConst c) {
       }
     }
     __syncthreads();
-#pragma unroll 4
-    for (int u = 0; u < n; ++u) {
-      const double2 w = TABLE ? tab[k] : dft_phase(k, nt);
-      k += step;
-      k = k >= nt ? k - nt : k;
+    for (int v0 = 0; v0 < n; v0 += DFT_BLOCK) {
+      double pa[DFT_LINES], pb[DFT_LINES], pc[DFT_LINES], pd[DFT_LINES];   // sums of a block
 #pragma unroll
-      for (int r = 0; r < DFT_LINES; ++r) {
-        if constexpr (MODE == 0) {
-          const double v = bd[u * DFT_LINES + r];
-          sa[r] = fmx(v, w.x, sa[r]);
-          sc[r] = fmx(v, w.y, sc[r]);
-        } else {
-          const double2 v = buf[u * DFT_LINES + r];
-          sa[r] = fmx(v.x, w.x, sa[r]);
-          sb[r] = fmx(v.y, w.y, sb[r]);
-          if constexpr (MODE != 3) {
-            sc[r] = fmx(v.x, w.y, sc[r]);
-            sd[r] = fmx(v.y, w.x, sd[r]);
+      for (int r = 0; r < DFT_LINES; ++r) pa[r] = pb[r] = pc[r] = pd[r] = 0.0;
+      const int v1 = min(v0 + DFT_BLOCK, n);
+#pragma unroll 4
+      for (int u = v0; u < v1; ++u) {
+        const double2 w = TABLE ? tab[k] : dft_phase(k, nt);
+        k += step;
+        k = k >= nt ? k - nt : k;
+#pragma unroll
+        for (int r = 0; r < DFT_LINES; ++r) {
+          if constexpr (MODE == 0) {
+            const double v = bd[u * DFT_LINES + r];
+            pa[r] = fmx(v, w.x, pa[r]);
+            pc[r] = fmx(v, w.y, pc[r]);
+          } else {
+            const double2 v = buf[u * DFT_LINES + r];
+            pa[r] = fmx(v.x, w.x, pa[r]);
+            pb[r] = fmx(v.y, w.y, pb[r]);
+            if constexpr (MODE != 3) {
+              pc[r] = fmx(v.x, w.y, pc[r]);
+              pd[r] = fmx(v.y, w.x, pd[r]);
+            }
           }
         }
+      }
+#pragma unroll
+      for (int r = 0; r < DFT_LINES; ++r) {
+        sa[r] += pa[r];
+        sb[r] += pb[r];
+        sc[r] += pc[r];
+        sd[r] += pd[r];
       }
     }
   }
@@ -163,8 +179,9 @@ k_dft(const double* __restrict__ in, double* __restrict__ out, DftConst c) {
 // The same four passes for small planes in one launch: a work-group holds one plane, its half
 // spectrum in LDS between the passes.  Up to 32 x 32, where the separate passes are bound by
 // their launches: four passes on 6 planes of 8 x 8 took 16 us, now 5.5 us, on 16 of 32 x 32 42 us, now 16 us; larger planes
-// leave too few work-groups busy (one per plane).
-constexpr int DFT_SMALL = 32, DFT_SMALL_BS = 512;
+// leave too few work-groups busy (one per plane).  Sums in blocks of 4 as above: 3.0e-16 of phi at nt =
+// 32, 2.5e-16 at 16 (3.9e-16 and 3.1e-16 with every term its own phase, no half spectrum).
+constexpr int DFT_SMALL = 32, DFT_SMALL_BS = 512, DFT_SMALL_BLOCK = 4;
 __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __restrict__ in, double* __restrict__ out,
                                                             DftConst c) {
   __shared__ double2 tab[DFT_SMALL];
@@ -178,13 +195,18 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
   for (int t = t0; t < nt * h; t += DFT_SMALL_BS) {
     const int x = t % h, y = t / h;
     double sr = 0.0, si = 0.0;
-    for (int u = 0, k = 0; u < nt; ++u) {
-      const double v = g[y * nt + u];
-      const double2 w = tab[k];
-      k += x;
-      k = k >= nt ? k - nt : k;
-      sr = fmx(v, w.x, sr);
-      si = fmx(-v, w.y, si);
+    for (int u = 0, k = 0; u < nt;) {
+      double pr = 0.0, pi = 0.0;
+      for (const int e = min(u + DFT_SMALL_BLOCK, nt); u < e; ++u) {
+        const double v = g[y * nt + u];
+        const double2 w = tab[k];
+        k += x;
+        k = k >= nt ? k - nt : k;
+        pr = fmx(v, w.x, pr);
+        pi = fmx(-v, w.y, pi);
+      }
+      sr += pr;
+      si += pi;
     }
     f[0][t] = make_double2(sr, si);
   }
@@ -194,14 +216,19 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
     for (int t = t0; t < nt * h; t += DFT_SMALL_BS) {
       const int x = t % h, y = t / h;
       double sr = 0.0, si = 0.0;
-      for (int u = 0, k = 0; u < nt; ++u) {
-        const double2 v = f[p][u * h + x];
-        const double2 w = tab[k];
-        k += y;
-        k = k >= nt ? k - nt : k;
-        const double wi = p == 0 ? -w.y : w.y;
-        sr = fmx(v.x, w.x, fmx(-v.y, wi, sr));
-        si = fmx(v.x, wi, fmx(v.y, w.x, si));
+      for (int u = 0, k = 0; u < nt;) {
+        double pr = 0.0, pi = 0.0;
+        for (const int e = min(u + DFT_SMALL_BLOCK, nt); u < e; ++u) {
+          const double2 v = f[p][u * h + x];
+          const double2 w = tab[k];
+          k += y;
+          k = k >= nt ? k - nt : k;
+          const double wi = p == 0 ? -w.y : w.y;
+          pr += fmx(v.x, w.x, -(v.y * wi));
+          pi += fmx(v.x, wi, v.y * w.x);
+        }
+        sr += pr;
+        si += pi;
       }
       const double q = p == 0 ? dft_filter(x, y, c) : 1.0;
       f[1 - p][t] = make_double2(q * sr, q * si);
@@ -211,13 +238,17 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
   for (int t = t0; t < n2; t += DFT_SMALL_BS) {
     const int x = t % nt, y = t / nt;
     double sr = 0.0;
-    for (int u = 0, k = 0; u < h; ++u) {
-      const double2 v = f[0][y * h + u];
-      const double2 w = tab[k];
-      k += x;
-      k = k >= nt ? k - nt : k;
-      const double m = (u == 0 || 2 * u == nt) ? 1.0 : 2.0;
-      sr = fmx(m * v.x, w.x, fmx(-m * v.y, w.y, sr));
+    for (int u = 0, k = 0; u < h;) {
+      double pr = 0.0;
+      for (const int e = min(u + DFT_SMALL_BLOCK, h); u < e; ++u) {
+        const double2 v = f[0][y * h + u];
+        const double2 w = tab[k];
+        k += x;
+        k = k >= nt ? k - nt : k;
+        const double m = (u == 0 || 2 * u == nt) ? 1.0 : 2.0;
+        pr += fmx(m * v.x, w.x, -(m * v.y * w.y));
+      }
+      sr += pr;
     }
     out[base + t] = sr / (double)n2;
   }

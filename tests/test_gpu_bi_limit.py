@@ -106,3 +106,44 @@ def test_transverse_field_sizes(nt):
     err = np.abs(got[2] - ez).max() / max(np.abs(ez).max(), 1e-300)
     print("  max error / max", err, flush=True)
     assert err < 1e-11 and np.abs(got[:2]).max() <= 1e-11 * np.abs(ez).max()
+
+
+@pytest.mark.parametrize("nt", [32, 192, 256])
+def test_transverse_field_rounding(nt):
+    """The rounding of phi: one colour per nucleus with |phi| ~ 40, so that phi's error decides that of
+    E_z (closed form as above), against phi in extended precision.  Sums of nt products in blocks of b
+    leave a relative rms error of a few times (sqrt(b) + sqrt(nt / b)) / 2 units of 2^-53 at most, where
+    plain sums leave sqrt(nt) / 2 in each of four passes: below 6 units for the blocks, about 8 and 9
+    units for plain sums of 192 and 256.  Bound: the error that independent errors of 6 units in phi
+    and 2 in the links' angles would make."""
+    pkg = lattice_or_skip()
+    print("case: transverse field rounding, nt", nt, flush=True)
+    if np.finfo(np.longdouble).eps > 2.0 ** -60:
+        pytest.skip("no extended precision here")
+    a_T, m = 4.0, 0.2
+    g = synth.rng(900 + nt)
+    rho = np.zeros((2, 3, nt, nt))
+    rho[0, 0], rho[1, 1] = g.standard_normal((2, nt, nt)) * 10.0
+    k = np.arange(nt, dtype=np.longdouble)
+    pi = np.longdouble("3.14159265358979323846264338327950288")
+    ph = (np.outer(np.arange(nt), np.arange(nt)) % nt).astype(np.longdouble) * 2 * pi / nt
+    W = np.cos(ph) - 1j * np.sin(ph)
+    s2 = (np.longdouble(2) / np.longdouble(a_T) * np.sin(pi * k / nt)) ** 2
+    filt = 1 / (s2[:, None] + s2[None, :] + np.longdouble(m) * np.longdouble(m))
+    phi = [np.real(np.conj(W) @ ((W @ r.astype(np.longdouble) @ W) * filt) @ np.conj(W)) / (nt * nt) for r in (rho[0, 0], rho[1, 1])]
+
+    def field(p):
+        ez = 0
+        for ax in (-1, -2):
+            al = [2 * np.sin((np.roll(q, -1, axis=ax) - q) / 2) / np.longdouble(a_T) for q in p]
+            ez = ez + 0.5 * (al[0] * al[1] + np.roll(al[0] * al[1], 1, axis=ax))
+        return ez
+
+    ref = field(phi)
+    rms = [np.sqrt(np.mean(q ** 2)) for q in phi]
+    off = [q + 2.0 ** -53 * np.sqrt(6.0 ** 2 + 2.0 ** 2) * r * g.standard_normal((nt, nt)) for q, r in zip(phi, rms)]
+    bound = np.sqrt(np.mean((field(off) - ref) ** 2))
+    got = pkg.boost_invariant_fields(2, nt, rho[0], rho[1], a_T=a_T, m_ir=m)["Ez"].cpu().numpy()[2]
+    err = np.sqrt(np.mean((got - ref) ** 2))
+    print("  |phi|", float(rms[0]), "rms error", float(err), "bound", float(bound), flush=True)
+    assert err <= bound
