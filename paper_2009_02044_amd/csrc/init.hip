@@ -72,6 +72,12 @@ __device__ __forceinline__ double dft_filter(int kx, int ky, const DftConst& c) 
   if (c.uv_cut > 0.0 && sqrt(k2) > c.uv_cut) return 0.0;
   return 1.0 / (k2 + c.m_ir * c.m_ir);
 }
+// The weight of a mode of the half spectrum: the mean of the filter at k and -k.  sinpi((nt - k) / nt)
+// rounds away from sinpi(k / nt), so a cut at a mode's |k~| can fall between the two; the real part of
+// the transform then holds half of the mode, along x as along y.
+__device__ __forceinline__ double dft_weight(int kx, int ky, const DftConst& c) {
+  return 0.5 * (dft_filter(kx, ky, c) + dft_filter(kx ? c.nt - kx : 0, ky ? c.nt - ky : 0, c));
+}
 // (held to few waves per SIMD: with registers for more, the compiler waits for every LDS read)
 template <int MODE, bool TABLE>
 __global__ void __launch_bounds__(DFT_BS) __attribute__((amdgpu_waves_per_eu(1, 2)))
@@ -165,7 +171,7 @@ k_dft(const double* __restrict__ in, double* __restrict__ out, DftConst c) {
       if constexpr (MODE == 3) {
         out[((int64_t)b * nt + l) * nt + q] = fmx(-s, sb[r], sa[r]) / ((double)nt * nt);
       } else {
-        const double f = MODE == 1 ? dft_filter(l, q, c) : 1.0;
+        const double f = MODE == 1 ? dft_weight(l, q, c) : 1.0;
         const int64_t at = ROWS ? ((int64_t)b * nt + l) * h + q : ((int64_t)b * nt + q) * h + l;
         ((double2*)out)[at] = make_double2(f * fmx(-s, sb[r], sa[r]), f * fmx(s, sc[r], sd[r]));
       }
@@ -230,7 +236,7 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
         sr += pr;
         si += pi;
       }
-      const double q = p == 0 ? dft_filter(x, y, c) : 1.0;
+      const double q = p == 0 ? dft_weight(x, y, c) : 1.0;
       f[1 - p][t] = make_double2(q * sr, q * si);
     }
     __syncthreads();

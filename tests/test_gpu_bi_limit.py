@@ -147,3 +147,29 @@ def test_transverse_field_rounding(nt):
     err = np.sqrt(np.mean((got - ref) ** 2))
     print("  |phi|", float(rms[0]), "rms error", float(err), "bound", float(bound), flush=True)
     assert err <= bound
+
+
+@pytest.mark.parametrize("nt", [27, 47, 97])
+@pytest.mark.parametrize("axis", [-1, -2])
+def test_cut_between_the_roundings_of_a_mode(nt, axis):
+    """A cut at a mode's |k~| can lie between sin(pi k / nt) and sin(pi (nt - k) / nt) as rounded (13 to 32
+    units of 2^-53 apart here): one of +-k is then left, so half of the mode, along x and along y
+    alike.  Plane waves of the lowest mode, one colour per nucleus, closed form as above."""
+    pkg = lattice_or_skip()
+    print("case: cut between roundings, nt", nt, "axis", axis, flush=True)
+    a_T, m = 4.0, 0.2
+    pi = np.longdouble("3.14159265358979323846264338327950288")
+    s = [np.sin(pi * np.longdouble(1.0 / nt)), np.sin(pi * (1 - np.longdouble((nt - 1) / nt)))]
+    cut = float(np.longdouble(2) / np.longdouble(a_T) * (s[0] + s[1]) / 2)
+    ang = 2 * np.pi * np.arange(nt) / nt
+    wave = [np.cos(ang), np.sin(ang)]
+    rho = np.zeros((2, 3, nt, nt))
+    for n in range(2):
+        rho[n, n] = 0.1 * (wave[n][None, :] if axis == -1 else wave[n][:, None])
+    phi = [0.5 * rho[n, n] / ((2 / a_T * np.sin(np.pi / nt)) ** 2 + m * m) for n in range(2)]
+    al = [2.0 * np.sin((np.roll(p, -1, axis=axis) - p) / 2) / a_T for p in phi]
+    ez = 0.5 * (al[0] * al[1] + np.roll(al[0] * al[1], 1, axis=axis))
+    got = pkg.boost_invariant_fields(2, nt, rho[0], rho[1], a_T=a_T, m_ir=m, uv_cut=cut)["Ez"].cpu().numpy()[2]
+    err = np.abs(got - ez).max() / np.abs(ez).max()
+    print("  max error / max", err, flush=True)
+    assert err < 1e-11
