@@ -78,6 +78,19 @@ __device__ __forceinline__ double dft_filter(int kx, int ky, const DftConst& c) 
 __device__ __forceinline__ double dft_weight(int kx, int ky, const DftConst& c) {
   return 0.5 * (dft_filter(kx, ky, c) + dft_filter(kx ? c.nt - kx : 0, ky ? c.nt - ky : 0, c));
 }
+// terms 0 .. n - 1 in blocks of B, done() after each
+template <int B, int UNROLL, typename F, typename D>
+__device__ __forceinline__ void in_blocks(int n, F&& term, D&& done) {
+  int u = 0;
+  for (; u + B <= n; u += B) {
+#pragma unroll UNROLL
+    for (int f = 0; f < B; ++f) term(u + f);
+    done();
+  }
+  if (u == n) return;
+  for (; u < n; ++u) term(u);
+  done();
+}
 // (held to few waves per SIMD: with registers for more, the compiler waits for every LDS read)
 template <int MODE, bool TABLE>
 __global__ void __launch_bounds__(DFT_BS) __attribute__((amdgpu_waves_per_eu(1, 2)))
@@ -125,41 +138,39 @@ k_dft(const double* __restrict__ in, double* __restrict__ out, DftConst c) {
       }
     }
     __syncthreads();
-    for (int v0 = 0; v0 < n; v0 += DFT_BLOCK) {
-      double pa[DFT_LINES], pb[DFT_LINES], pc[DFT_LINES], pd[DFT_LINES];   // sums of a block
+    double pa[DFT_LINES], pb[DFT_LINES], pc[DFT_LINES], pd[DFT_LINES];   // sums of a block
 #pragma unroll
-      for (int r = 0; r < DFT_LINES; ++r) pa[r] = pb[r] = pc[r] = pd[r] = 0.0;
-      const int v1 = min(v0 + DFT_BLOCK, n);
-#pragma unroll 4
-      for (int u = v0; u < v1; ++u) {
-        const double2 w = TABLE ? tab[k] : dft_phase(k, nt);
-        k += step;
-        k = k >= nt ? k - nt : k;
+    for (int r = 0; r < DFT_LINES; ++r) pa[r] = pb[r] = pc[r] = pd[r] = 0.0;
+    in_blocks<DFT_BLOCK, 4>(n, [&](int u) __attribute__((always_inline)) {
+      const double2 w = TABLE ? tab[k] : dft_phase(k, nt);
+      k += step;
+      k = k >= nt ? k - nt : k;
 #pragma unroll
-        for (int r = 0; r < DFT_LINES; ++r) {
-          if constexpr (MODE == 0) {
-            const double v = bd[u * DFT_LINES + r];
-            pa[r] = fmx(v, w.x, pa[r]);
-            pc[r] = fmx(v, w.y, pc[r]);
-          } else {
-            const double2 v = buf[u * DFT_LINES + r];
-            pa[r] = fmx(v.x, w.x, pa[r]);
-            pb[r] = fmx(v.y, w.y, pb[r]);
-            if constexpr (MODE != 3) {
-              pc[r] = fmx(v.x, w.y, pc[r]);
-              pd[r] = fmx(v.y, w.x, pd[r]);
-            }
+      for (int r = 0; r < DFT_LINES; ++r) {
+        if constexpr (MODE == 0) {
+          const double v = bd[u * DFT_LINES + r];
+          pa[r] = fmx(v, w.x, pa[r]);
+          pc[r] = fmx(v, w.y, pc[r]);
+        } else {
+          const double2 v = buf[u * DFT_LINES + r];
+          pa[r] = fmx(v.x, w.x, pa[r]);
+          pb[r] = fmx(v.y, w.y, pb[r]);
+          if constexpr (MODE != 3) {
+            pc[r] = fmx(v.x, w.y, pc[r]);
+            pd[r] = fmx(v.y, w.x, pd[r]);
           }
         }
       }
+    }, [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int r = 0; r < DFT_LINES; ++r) {
         sa[r] += pa[r];
         sb[r] += pb[r];
         sc[r] += pc[r];
         sd[r] += pd[r];
+        pa[r] = pb[r] = pc[r] = pd[r] = 0.0;
       }
-    }
+    });
   }
   if (o >= h) return;
   const bool both = MODE != 0 && o != 0 && 2 * o != nt;
@@ -200,20 +211,17 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
   __syncthreads();
   for (int t = t0; t < nt * h; t += DFT_SMALL_BS) {
     const int x = t % h, y = t / h;
-    double sr = 0.0, si = 0.0;
-    for (int u = 0, k = 0; u < nt;) {
-      double pr = 0.0, pi = 0.0;
-      for (const int e = min(u + DFT_SMALL_BLOCK, nt); u < e; ++u) {
-        const double v = g[y * nt + u];
-        const double2 w = tab[k];
-        k += x;
-        k = k >= nt ? k - nt : k;
-        pr = fmx(v, w.x, pr);
-        pi = fmx(-v, w.y, pi);
-      }
-      sr += pr;
-      si += pi;
-    }
+    double sr = 0.0, si = 0.0, pr = 0.0, pi = 0.0;
+    int k = 0;
+    auto done = [&]() { sr += pr; si += pi; pr = pi = 0.0; };
+    in_blocks<DFT_SMALL_BLOCK, DFT_SMALL_BLOCK>(nt, [&](int u) {
+      const double v = g[y * nt + u];
+      const double2 w = tab[k];
+      k += x;
+      k = k >= nt ? k - nt : k;
+      pr = fmx(v, w.x, pr);
+      pi = fmx(-v, w.y, pi);
+    }, done);
     f[0][t] = make_double2(sr, si);
   }
   __syncthreads();
@@ -221,21 +229,18 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
   for (int p = 0; p < 2; ++p) {   // along y: forward with the filter, then inverse
     for (int t = t0; t < nt * h; t += DFT_SMALL_BS) {
       const int x = t % h, y = t / h;
-      double sr = 0.0, si = 0.0;
-      for (int u = 0, k = 0; u < nt;) {
-        double pr = 0.0, pi = 0.0;
-        for (const int e = min(u + DFT_SMALL_BLOCK, nt); u < e; ++u) {
-          const double2 v = f[p][u * h + x];
-          const double2 w = tab[k];
-          k += y;
-          k = k >= nt ? k - nt : k;
-          const double wi = p == 0 ? -w.y : w.y;
-          pr += fmx(v.x, w.x, -(v.y * wi));
-          pi += fmx(v.x, wi, v.y * w.x);
-        }
-        sr += pr;
-        si += pi;
-      }
+      double sr = 0.0, si = 0.0, pr = 0.0, pi = 0.0;
+      int k = 0;
+      auto done = [&]() { sr += pr; si += pi; pr = pi = 0.0; };
+      in_blocks<DFT_SMALL_BLOCK, DFT_SMALL_BLOCK>(nt, [&](int u) {
+        const double2 v = f[p][u * h + x];
+        const double2 w = tab[k];
+        k += y;
+        k = k >= nt ? k - nt : k;
+        const double wi = p == 0 ? -w.y : w.y;
+        pr += fmx(v.x, w.x, -(v.y * wi));
+        pi += fmx(v.x, wi, v.y * w.x);
+      }, done);
       const double q = p == 0 ? dft_weight(x, y, c) : 1.0;
       f[1 - p][t] = make_double2(q * sr, q * si);
     }
@@ -243,19 +248,17 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
   }
   for (int t = t0; t < n2; t += DFT_SMALL_BS) {
     const int x = t % nt, y = t / nt;
-    double sr = 0.0;
-    for (int u = 0, k = 0; u < h;) {
-      double pr = 0.0;
-      for (const int e = min(u + DFT_SMALL_BLOCK, h); u < e; ++u) {
-        const double2 v = f[0][y * h + u];
-        const double2 w = tab[k];
-        k += x;
-        k = k >= nt ? k - nt : k;
-        const double m = (u == 0 || 2 * u == nt) ? 1.0 : 2.0;
-        pr += fmx(m * v.x, w.x, -(m * v.y * w.y));
-      }
-      sr += pr;
-    }
+    double sr = 0.0, pr = 0.0;
+    int k = 0;
+    auto done = [&]() { sr += pr; pr = 0.0; };
+    in_blocks<DFT_SMALL_BLOCK, DFT_SMALL_BLOCK>(h, [&](int u) {
+      const double2 v = f[0][y * h + u];
+      const double2 w = tab[k];
+      k += x;
+      k = k >= nt ? k - nt : k;
+      const double m = (u == 0 || 2 * u == nt) ? 1.0 : 2.0;
+      pr += fmx(m * v.x, w.x, -(m * v.y * w.y));
+    }, done);
     out[base + t] = sr / (double)n2;
   }
 }
@@ -281,126 +284,132 @@ __device__ typename Gd::Link wilson(const double* __restrict__ phi, int ns, int 
   return V;
 }
 
-__device__ __forceinline__ double profileA(double z, double tau, const McvConst& mv) {
-  return 0.5 * erfc(-(z - mv.zA + tau) / (1.4142135623730951 * mv.sigma));
+// distance ahead of the nucleus's centre (A moves -z)
+__device__ __forceinline__ double aheadA(double z, double tau, const McvConst& mv) { return -(z - mv.zA + tau); }
+__device__ __forceinline__ double aheadB(double z, double tau, const McvConst& mv) { return z - mv.zB - tau; }
+__device__ __forceinline__ double profile(double ahead, const McvConst& mv) {
+  return 0.5 * erfc(ahead / (1.4142135623730951 * mv.sigma));
 }
-__device__ __forceinline__ double profileB(double z, double tau, const McvConst& mv) {
-  return 0.5 * erfc((z - mv.zB - tau) / (1.4142135623730951 * mv.sigma));
+__device__ __forceinline__ double of_lane(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Links and E of one tile of IC_TX x IC_TX transverse sites at one z per work-group.  A transverse
-// link of nucleus N is V_N(x) V_N^dag(x + i), and V_N belongs to a site: each is formed once per
-// tile (and once more per neighbouring tile, on the tile's +x and +y rim) and read from LDS
-// by the sites that need it, two nuclei and two times in turn.  Bound by FP64 arithmetic; with
-// every site forming its neighbours' V itself (16 exponentials per site and sheet instead of 4.5)
-// 512 x 64 x 64 took 0.82 ms and 1.81 ms with 8 sheets, now 0.41 and 0.59 ms.
+// all reals of a matrix
+template <typename T> struct FullWidth;
+template <> struct FullWidth<Q2<double>> { static constexpr int value = 4; };
+template <> struct FullWidth<M3<double>> { static constexpr int value = 18; };
+__device__ __forceinline__ double& full_real(Q2<double>& l, int k) { return l.q[k]; }
+__device__ __forceinline__ double& full_real(M3<double>& l, int k) {
+  return k & 1 ? l.im[k / 6][k % 6 / 2] : l.re[k / 6][k % 6 / 2];
+}
+
+// Links and E of one tile of IC_TX x IC_TY transverse sites at one z per work-group.  A transverse link
+// of nucleus N is V_N(x) V_N^dag(x + i), and V_N belongs to a site: each is formed once per tile (and
+// once more per neighbouring tile, on the tile's +x and +y rim) and read from LDS by the threads that
+// need it, both nuclei at a time, the two times in turn.  SU(3): a thread per link (the first half of the
+// work-group x links, the other y links); SU(2): a thread per site.
+// Matrices between the exponentials and the stored link are held whole: by two rows, the third
+// rebuilt, SU(3) E is 7% (1 sheet) to 19% (8 sheets) further off.  Bound by FP64 arithmetic; with every
+// site forming its neighbours' V itself (16 exponentials per site and sheet instead of 4.8) 512 x 64 x 64
+// took 0.81 ms and 1.89 ms with 8 sheets, now 0.43 and 0.71 ms (0.40 and 0.64 ms by two rows).
 // Layers that the profiles of both times reach equally (the flat parts) take U(t0 - dt) = U(t0).
-constexpr int IC_TX = 16, IC_BS = IC_TX * IC_TX, IC_RIM = IC_TX + 1;
+constexpr int IC_BS = 256, IC_TX = 16, IC_RIM = IC_TX + 1;
+template <typename Gd> constexpr int IC_LINKS = Gd::NC == 3 ? 1 : 2;   // of a thread
+template <typename Gd> constexpr int IC_TY = IC_BS * IC_LINKS<Gd> / 2 / IC_TX;
 template <typename Gd, typename T>
 __global__ void __launch_bounds__(IC_BS, 2) k_ic_links(const double* __restrict__ phi, int ns, T* __restrict__ U,
                                                        T* __restrict__ E, Geom g, StepConst c, McvConst mv, int z_first) {
   using L = typename Gd::Link;
   using A = typename Gd::Alg;
-  constexpr int NG = Gd::NG, W = StoredWidth<L>::value;
-  // V as stored (SU(3): two rows), component k of tile site p at v[k * PITCH + p]
-  constexpr int PITCH = IC_RIM * IC_RIM;
-  __shared__ double v[W * PITCH];
-  __shared__ double u1[2 * W * IC_BS];   // U(t0 - dt) of the thread's x and y links
-  const int x0 = blockIdx.x * IC_TX, y0 = blockIdx.y * IC_TX;
-  const int tx = threadIdx.x % IC_TX, ty = threadIdx.x / IC_TX;
+  constexpr int NG = Gd::NG, W = FullWidth<L>::value, NL = IC_LINKS<Gd>;
+  constexpr int SITES = IC_TX * IC_TY<Gd>, PITCH = IC_RIM * (IC_TY<Gd> + 1);
+  __shared__ double v[2 * W * PITCH];   // V_N, real k of tile site p at v[(N W + k) PITCH + p]
+  const int x0 = blockIdx.x * IC_TX, y0 = blockIdx.y * IC_TY<Gd>;
+  const int i0 = __builtin_amdgcn_readfirstlane(threadIdx.x / SITES);   // first direction (uniform over a wavefront)
+  const int tx = threadIdx.x % IC_TX, ty = threadIdx.x % SITES / IC_TX;
   const bool has = x0 + tx < g.nt && y0 + ty < g.nt;
   const uint32_t t = (uint32_t)(min(y0 + ty, g.nt - 1) * g.nt + min(x0 + tx, g.nt - 1));
   const int z = z_first + (int)blockIdx.z;
   if (z == g.nz) {   // the z links of the periodic seam, in work-groups of their own
-    if (!has) return;
+    if (!has || i0) return;
     const double zs = (g.nz - 1) * c.a[2];
-    L us[2];
+    const uint32_t s = (uint32_t)((g.nz - 1) * g.layer) + t;
+    double* park = v + threadIdx.x;   // U(t0), a slot per thread (SITES < PITCH of them)
+    L us;
 #pragma unroll 1
     for (int q = 0; q < 2; ++q) {
       const double tau = q == 0 ? 0.0 : -c.dt;
-      const L VA = wilson<Gd>(phi, ns, 0, t, g.layer, profileA(zs, tau, mv));
-      us[1] = us[0];
-      us[0] = Gd::mul_dag(VA, wilson<Gd>(phi, ns, 1, t, g.layer, profileB(0.0, tau, mv)));
+      us = wilson<Gd>(phi, ns, 0, t, g.layer, profile(aheadA(zs, tau, mv), mv));
+      us = Gd::mul_dag(us, wilson<Gd>(phi, ns, 1, t, g.layer, profile(aheadB(0.0, tau, mv), mv)));
+      if (q == 0) {
+        store_link(us, U, 2, s, g.Vp);
+#pragma unroll
+        for (int k = 0; k < W; ++k) park[k * PITCH] = full_real(us, k);
+      }
     }
-    A e = Gd::logi(Gd::mul_dag(us[1], us[0]));
+    L u0;
+#pragma unroll
+    for (int k = 0; k < W; ++k) full_real(u0, k) = park[k * PITCH];
+    A e = Gd::logi(Gd::mul_dag(u0, us));
     const double k = 1.0 / (c.a[2] * c.dt);
 #pragma unroll
     for (int q = 0; q < NG; ++q) e.c[q] *= k;
-    const uint32_t s = (uint32_t)((g.nz - 1) * g.layer) + t;
-    store_link(us[1], U, 2, s, g.Vp);
     store_alg(e, E, 2, s, g.Vp);
     return;
   }
   const uint32_t s = (uint32_t)(z * g.layer) + t;
-  auto get = [&](int p) -> L {
-    double b[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) b[k] = v[k * PITCH + p];
+  auto get = [&](int nucleus, int p) -> L {
     L l;
-    link_from_stored(l, b);
+#pragma unroll
+    for (int k = 0; k < W; ++k) full_real(l, k) = v[(nucleus * W + k) * PITCH + p];
     return l;
   };
-  const double zz = z * c.a[2];
-  const double lA[2] = {profileA(zz, 0.0, mv), profileA(zz, -c.dt, mv)};
-  const double lB[2] = {profileB(zz, 0.0, mv), profileB(zz, -c.dt, mv)};
+  // the layer's four profile weights, one per lane (an error function each, a fifth of the kernel
+  // when every thread formed all four)
+  const double zz = z * c.a[2], tau = threadIdx.x & 1 ? -c.dt : 0.0;
+  const double w4 = profile(threadIdx.x & 2 ? aheadB(zz, tau, mv) : aheadA(zz, tau, mv), mv);
+  const double lA[2] = {of_lane(w4, 0), of_lane(w4, 1)}, lB[2] = {of_lane(w4, 2), of_lane(w4, 3)};
   const bool flat = lA[0] == lA[1] && lB[0] == lB[1];
-  double r[2][W];   // x and y link of the nuclei done so far, as stored
+  L u[NL], u1[NL];   // at t0 and at t0 - dt
 #pragma unroll 1
-  for (int q = flat ? 2 : 0; q < 4; ++q) {   // (t0 - dt, A), (t0 - dt, B), (t0, A), (t0, B)
-    const int time = q < 2 ? 1 : 0, nucleus = q & 1;
-    const double lam = nucleus == 0 ? (time ? lA[1] : lA[0]) : (time ? lB[1] : lB[0]);
+  for (int time = flat ? 0 : 1; time >= 0; --time) {
+    const double wA = time ? lA[1] : lA[0], wB = time ? lB[1] : lB[0];
     __syncthreads();
-    for (int p = threadIdx.x; p < PITCH; p += IC_BS) {
-      const int px = x0 + p % IC_RIM, py = y0 + p / IC_RIM;
+    for (int p = threadIdx.x; p < 2 * PITCH; p += IC_BS) {
+      const int nucleus = p >= PITCH ? 1 : 0, r = p - nucleus * PITCH;
+      const int px = x0 + r % IC_RIM, py = y0 + r / IC_RIM;
       if (px > g.nt || py > g.nt) continue;   // beyond the rim of a short tile
-      const L V = wilson<Gd>(phi, ns, nucleus, (int64_t)(py % g.nt) * g.nt + px % g.nt, g.layer, lam);
-      double b[W];
-      stored_of(V, b);
+      L V = wilson<Gd>(phi, ns, nucleus, (int64_t)(py % g.nt) * g.nt + px % g.nt, g.layer, nucleus ? wB : wA);
 #pragma unroll
-      for (int k = 0; k < W; ++k) v[k * PITCH + p] = b[k];
+      for (int k = 0; k < W; ++k) v[(nucleus * W + k) * PITCH + r] = full_real(V, k);
     }
     __syncthreads();
     if (!has) continue;
     const int p = ty * IC_RIM + tx;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      L D = Gd::mul_dag(get(p), get(p + (i == 0 ? 1 : IC_RIM)));
-      if (nucleus == 1) {
-        L l;
-        link_from_stored(l, r[i]);
-        D = Gd::mul(l, D);
-      }
-      stored_of(D, r[i]);
-      if (q == 1) {
-#pragma unroll
-        for (int k = 0; k < W; ++k) u1[(i * W + k) * IC_BS + threadIdx.x] = r[i][k];
-      }
+    for (int n = 0; n < NL; ++n) {
+      const int pn = p + (i0 + n == 0 ? 1 : IC_RIM);
+      const L D = Gd::mul_dag(get(0, p), get(0, pn));
+      if (time) u1[n] = Gd::mul(D, Gd::mul_dag(get(1, p), get(1, pn)));
+      else u[n] = Gd::mul(D, Gd::mul_dag(get(1, p), get(1, pn)));
     }
   }
   if (!has) return;
-#pragma unroll 1
-  for (int i = 0; i < 2; ++i) {
-    L U0, U1;
+  const double k = 1.0 / (c.a[0] * c.dt);
+#pragma unroll
+  for (int n = 0; n < NL; ++n) {
     A e = Gd::alg_zero();
-    double b[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) b[k] = i == 0 ? r[0][k] : r[1][k];
-    link_from_stored(U0, b);
-    if (!flat) {
-#pragma unroll
-      for (int k = 0; k < W; ++k) b[k] = u1[(i * W + k) * IC_BS + threadIdx.x];
-      link_from_stored(U1, b);
-      e = Gd::logi(Gd::mul_dag(U0, U1));
-    }
-    const double k = 1.0 / (c.a[0] * c.dt);
+    if (!flat) e = Gd::logi(Gd::mul_dag(u[n], u1[n]));
 #pragma unroll
     for (int q = 0; q < NG; ++q) e.c[q] *= k;
-    store_link(U0, U, i, s, g.Vp);
-    store_alg(e, E, i, s, g.Vp);
+    store_link(u[n], U, i0 + n, s, g.Vp);
+    store_alg(e, E, i0 + n, s, g.Vp);
   }
   if (z < g.nz - 1) {
-    store_link(Gd::one(), U, 2, s, g.Vp);
-    store_alg(Gd::alg_zero(), E, 2, s, g.Vp);
+    if (NL == 2 || i0 == 0) store_link(Gd::one(), U, 2, s, g.Vp);
+    if (NL == 2 || i0 == 1) store_alg(Gd::alg_zero(), E, 2, s, g.Vp);
   }
 }
 
@@ -470,10 +479,10 @@ void launch_ic_fields(const double* phi, int ns, T* U, T* E, T* rhoA, T* rhoB, c
   using Gd = typename GroupOf<G::NC, double>::type;
   const int bs = 256;
   const unsigned sb = (unsigned)((g.V + bs - 1) / bs);
-  const unsigned nx = (unsigned)((g.nt + IC_TX - 1) / IC_TX);
+  const unsigned nx = (unsigned)((g.nt + IC_TX - 1) / IC_TX), ny = (unsigned)((g.nt + IC_TY<Gd> - 1) / IC_TY<Gd>);
   // layers 0 .. nz - 1 and the seam, as many at a time as a grid's third dimension takes
   for (int z = 0; z <= g.nz; z += 32768)
-    hipLaunchKernelGGL((k_ic_links<Gd, T>), dim3(nx, nx, (unsigned)std::min(32768, g.nz + 1 - z)), dim3(IC_BS), 0, st,
+    hipLaunchKernelGGL((k_ic_links<Gd, T>), dim3(nx, ny, (unsigned)std::min(32768, g.nz + 1 - z)), dim3(IC_BS), 0, st,
                        phi, ns, U, E, g, c, mv, z);
   // the semi-implicit scheme conserves D.(E + dt f1(U(t0), U(t0 - dt))) - rho instead;
   // its caller builds f1 and sets the charges through launch_gauss_charges

@@ -7,6 +7,7 @@ import pytest
 
 import synth
 from oracle import lattice, init_mv
+from scipy.special import erfc
 from _gpu import gpu, lattice_or_skip, to_comp, state_errs, mv_setup, new_lattice
 
 pytestmark = gpu
@@ -102,3 +103,111 @@ def test_init_tile_edges(nc, nz, nt, ns):
     errs = state_errs(lat.get_state(), st)
     print(" ", errs, flush=True)
     assert max(errs.values()) < 1e-10, errs
+
+
+def test_initial_field_of_whole_matrices():
+    """The rounding of E(t0 - dt/2) after 8 sheets, SU(3): rms error over all transverse links against
+    extended precision, compared with that of the same group operations on whole matrices (the library's
+    own, run on the host; same sequence of exponentials and products, profiles in double as well).  The
+    fields are weak (|phi| ~ 0.05 a sheet), so that the matrices' rounding decides and not that of phi
+    (3e-16 of E).  The device's error function adds its own rounding: half a unit 2^-53 rms in the two
+    profiles that E is the difference of, over dt times the profile's density at the centre.  Bound: both
+    together, and a tenth.  With intermediate matrices cut to two rows the error is half as large again."""
+    pkg = lattice_or_skip()
+    mp = pytest.importorskip("mpmath")
+    if np.finfo(np.longdouble).eps > 2.0 ** -60:
+        pytest.skip("no extended precision here")
+    nc, nz, nt, ns, a_T, dt, m = 3, 16, 16, 8, 4.0, 0.5, 0.2
+    sigma, zA, zB = 3.0, 9.0, 6.0
+    say("case: rounding of the initial field", nz, nt, ns)
+    g = synth.rng(951)
+    rho = g.standard_normal((2, ns, 8, nt, nt)) * 0.1 / (a_T * np.sqrt(ns))
+    lat = pkg.Lattice(nc=nc, nz=nz, nt=nt, a_T=a_T, dt=dt)
+    lat.init_mv(rho[0], rho[1], m_ir=m, sigma=sigma, zA=zA, zB=zB)
+    got = lat.get_state()["E"][:2].reshape(2, 8, nz, nt, nt)
+
+    ld = np.longdouble
+    pi = ld("3.14159265358979323846264338327950288")
+    ph = (np.outer(np.arange(nt), np.arange(nt)) % nt).astype(ld) * 2 * pi / nt
+    W = np.cos(ph) - 1j * np.sin(ph)
+    s2 = (ld(2) / ld(a_T) * np.sin(pi * np.arange(nt, dtype=ld) / nt)) ** 2
+    filt = 1 / (s2[:, None] + s2[None, :] + ld(m) * ld(m))
+    phi = np.real(np.conj(W) @ ((W @ rho.astype(ld) @ W) * filt) @ np.conj(W)) / (nt * nt)   # (2, ns, 8, y, x)
+    with mp.workdps(30):
+        wt = np.array([[[ld(mp.nstr(mp.erfc(d / (mp.sqrt(2) * sigma)) / 2, 25)) for d in
+                         (-(z - zA + tau) if n == 0 else z - zB - tau for z in range(nz))] for tau in (0.0, -dt)]
+                       for n in range(2)])                                    # (nucleus, time, z)
+    r3 = 1 / np.sqrt(ld(3))
+    t = np.zeros((8, 3, 3), np.clongdouble)
+    for a, (i, j) in enumerate([(0, 1), (0, 1), (0, 0), (0, 2), (0, 2), (1, 2), (1, 2), (2, 2)]):
+        if a == 2:
+            t[a] = np.diag([1, -1, 0]) / 2
+        elif a == 7:
+            t[a] = np.diag([r3, r3, -2 * r3]) / 2
+        elif a in (0, 3, 5):
+            t[a, i, j] = t[a, j, i] = 0.5
+        else:
+            t[a, i, j], t[a, j, i] = -0.5j, 0.5j
+    comps = lambda h: np.stack([2 * np.real(sum(t[a][i, j] * h[..., j, i] for i in range(3) for j in range(3)))
+                                for a in range(8)], -1)
+    dag = lambda x: np.conj(np.swapaxes(x, -1, -2))
+
+    def proj(x):
+        y = (x - dag(x)) / 2j
+        return y - np.trace(y, axis1=-2, axis2=-1)[..., None, None] / 3 * np.eye(3)
+
+    def expi(h):
+        x, out = 1j * h / 64, np.eye(3) + 0 * h
+        for n in range(18, 0, -1):
+            out = np.eye(3) + x @ out / n
+        for _ in range(6):
+            out = out @ out
+        return out
+
+    def log(w):
+        h = proj(w)
+        for _ in range(6):
+            e = expi(-h / 2)
+            h = h + proj(e @ w @ e)
+        return h
+
+    # extended precision, and the host's group operations in double, the profiles too: V (z, y, x)
+    wd = np.array([[0.5 * erfc(np.array([-(z - zA + tau) if n == 0 else z - zB - tau for z in range(nz)]) /
+                               (1.4142135623730951 * sigma)) for tau in (0.0, -dt)] for n in range(2)])
+    weight = lambda v, n, time, k: np.clip(ns * v[n, time] - k, 0, 1)
+    link = lambda r: r.reshape(-1, 18)
+    hmul = lambda a, b: pkg.host_group_op(3, 64, 6, np.concatenate([a, b], 1), 18)
+
+    def hdag(r):
+        q = r.reshape(-1, 3, 3, 2).transpose(0, 2, 1, 3).copy()
+        q[..., 1] *= -1
+        return link(np.ascontiguousarray(q))
+
+    U, H = {}, {}
+    for time in range(2):
+        D, F = [None, None], [None, None]
+        for n in range(2):
+            V = F_ = None
+            for k in range(ns):
+                lam = weight(wt, n, time, k)
+                mat = np.einsum("ayx,aij->yxij", phi[n, k], t)
+                e = expi(-lam[:, None, None, None, None] * mat[None])
+                V = e if V is None else V @ e
+                c = np.broadcast_to(phi[n, k].astype(float).transpose(1, 2, 0), (nz, nt, nt, 8)).reshape(-1, 8)
+                s = np.repeat(-weight(wd, n, time, k), nt * nt)[:, None]
+                x = pkg.host_group_op(3, 64, 0, np.concatenate([s, c], 1), 18)
+                F_ = x if F_ is None else np.where(s < 0, hmul(F_, x), F_)
+            D[n] = [V @ dag(np.roll(V, -1, axis=2 - i)) for i in range(2)]
+            F4 = F_.reshape(nz, nt, nt, 18)
+            F[n] = [hmul(F_, hdag(link(np.ascontiguousarray(np.roll(F4, -1, axis=2 - i))))) for i in range(2)]
+        U[time] = [D[0][i] @ D[1][i] for i in range(2)]
+        H[time] = [hmul(F[0][i], F[1][i]) for i in range(2)]
+    ref = np.stack([comps(log(U[0][i] @ dag(U[1][i]))) for i in range(2)]) / (ld(a_T) * ld(dt))
+    host = np.stack([pkg.host_group_op(3, 64, 1, hmul(H[0][i], hdag(H[1][i])), 8).reshape(nz, nt, nt, 8)
+                     for i in range(2)]) * (1.0 / (a_T * dt))
+    got = got.transpose(0, 2, 3, 4, 1)
+    size = np.sqrt(np.mean(ref ** 2))
+    eg, eh = (float(np.sqrt(np.mean((x - ref) ** 2)) / size) for x in (got, host))
+    say("  rms error of E / rms E: kernel", eg, "whole matrices on the host", eh)
+    profiles = np.sqrt(2) * 2.0 ** -54 / (dt / (np.sqrt(2 * np.pi) * sigma))
+    assert eg <= 1.1 * np.hypot(eh, profiles)
