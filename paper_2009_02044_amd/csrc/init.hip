@@ -400,10 +400,16 @@ __global__ void __launch_bounds__(IC_BS, 2) k_ic_links(const double* __restrict_
   const double k = 1.0 / (c.a[0] * c.dt);
 #pragma unroll
   for (int n = 0; n < NL; ++n) {
-    A e = Gd::alg_zero();
-    if (!flat) e = Gd::logi(Gd::mul_dag(u[n], u1[n]));
+    A e;
+    if (!flat) {
+      e = Gd::logi(Gd::mul_dag(u[n], u1[n]));
 #pragma unroll
-    for (int q = 0; q < NG; ++q) e.c[q] *= k;
+      for (int q = 0; q < NG; ++q) e.c[q] *= k;
+    } else {   // zero, or NaN where the links are not finite
+      const double o = full_real(u[n], 0) - full_real(u[n], 0);
+#pragma unroll
+      for (int q = 0; q < NG; ++q) e.c[q] = o;
+    }
     store_link(u[n], U, i0 + n, s, g.Vp);
     store_alg(e, E, i0 + n, s, g.Vp);
   }

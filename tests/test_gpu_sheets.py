@@ -211,3 +211,25 @@ def test_initial_field_of_whole_matrices():
     say("  rms error of E / rms E: kernel", eg, "whole matrices on the host", eh)
     profiles = np.sqrt(2) * 2.0 ** -54 / (dt / (np.sqrt(2 * np.pi) * sigma))
     assert eg <= 1.1 * np.hypot(eh, profiles)
+
+
+@pytest.mark.parametrize("nc", [2, 3])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_non_finite_charges_reach_every_layer(nc, value):
+    """One non-finite charge makes phi of its colour non-finite everywhere (a sum over all modes), so U and
+    E(t0 - dt/2) of every transverse link are, also in layers that the profiles of both times reach
+    equally, where E is not formed from a logarithm."""
+    pkg = lattice_or_skip()
+    nz, nt = 64, 16
+    say("case: non-finite charge", nc, value)
+    rho = np.full((nc * nc - 1, nt, nt), 0.01)
+    bad = rho.copy()
+    bad[1, 3, 5] = value
+    lat = pkg.Lattice(nc=nc, nz=nz, nt=nt)
+    lat.init_mv(bad, rho, sigma=0.35)
+    got = lat.get_state()
+    for k in ("U", "E"):
+        f = got[k][:2].reshape(2, -1, nz, nt * nt)
+        assert not np.isfinite(f).all(axis=1).any(), k
+    lat.init_mv(rho, rho, sigma=0.35)
+    assert all(np.isfinite(lat.get_state()[k]).all() for k in ("U", "E", "rhoA", "rhoB"))
