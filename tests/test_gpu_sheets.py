@@ -233,3 +233,21 @@ def test_non_finite_charges_reach_every_layer(nc, value):
         assert not np.isfinite(f).all(axis=1).any(), k
     lat.init_mv(rho, rho, sigma=0.35)
     assert all(np.isfinite(lat.get_state()[k]).all() for k in ("U", "E", "rhoA", "rhoB"))
+
+
+@pytest.mark.parametrize("nc,nz", [(2, 32768), (3, 32770)])
+def test_init_of_more_layers_than_a_grid_takes(nc, nz):
+    """The initial links come in launches of at most 32768 layers: the seam alone in the second (nz =
+    32768), two layers and the seam in the second (32770).  Nucleus A sits at the end, so that fields cross
+    from one launch into the next; links, E and charges against the oracle to 1e-10."""
+    pkg = lattice_or_skip()
+    w = synth.Workload(f"su{nc}-{nz}x2", nc=nc, nz=nz, nt=2, mu=0.5, sigma=2.0, seed=860 + nc, zA=nz - 6.0, zB=40.0)
+    say("case: layers", w.name)
+    p, mv = mv_setup(w)
+    rA, rB = synth.mv_charges(w.seed, nc, 2, w.mu, w.a_T)
+    st, _ = init_mv.initial_state(rA, rB, nz, p, mv)
+    lat = new_lattice(pkg, w)
+    lat.init_mv(rA, rB, m_ir=w.m_ir, uv_cut=w.uv_cut, sigma=w.sigma, zA=w.zA, zB=w.zB)
+    errs = state_errs(lat.get_state(), st)
+    say(" ", errs)
+    assert max(errs.values()) < 1e-10, errs
