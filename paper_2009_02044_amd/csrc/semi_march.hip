@@ -23,6 +23,40 @@ namespace gl {
 
 namespace {
 
+// Products of the march.  SU(2): each component one chain of fused multiply-adds, the largest product
+// last: links are near 1, so the terms without the zeroth component are small, and with them first
+// single precision leaves 0.70 of the error in E that the compiler's own choice of fused terms leaves
+// per direction (semi.hip), the other way round 1.2.
+template <typename G> struct MarchOps : G {};
+template <typename T> struct MarchOps<Su2<T>> : Su2<T> {
+  using L = Q2<T>;
+  using A = Alg2<T>;
+  // component k > 0 of a b: a0 b_k + a_k b0 - (a x b)_k
+  static __device__ __forceinline__ T vec(const L& a, const L& b, int k, int i, int j) {
+    return fmx(a.q[0], b.q[k], fmx(a.q[k], b.q[0], -fmx(a.q[i], b.q[j], -(a.q[j] * b.q[i]))));
+  }
+  static __device__ __forceinline__ L mul(const L& a, const L& b) {
+    L r;
+    r.q[0] = fmx(a.q[0], b.q[0], -fmx(a.q[1], b.q[1], fmx(a.q[2], b.q[2], a.q[3] * b.q[3])));
+    r.q[1] = vec(a, b, 1, 2, 3);
+    r.q[2] = vec(a, b, 2, 3, 1);
+    r.q[3] = vec(a, b, 3, 1, 2);
+    return r;
+  }
+  static __device__ __forceinline__ L mul_dag(const L& a, const L& b) { return mul(a, Su2<T>::dag(b)); }
+  static __device__ __forceinline__ A proj_mul_dag(const L& a, const L& b) {
+    const L c = Su2<T>::dag(b);
+    A r;
+    r.c[0] = 2 * vec(a, c, 1, 2, 3);
+    r.c[1] = 2 * vec(a, c, 2, 3, 1);
+    r.c[2] = 2 * vec(a, c, 3, 1, 2);
+    return r;
+  }
+  static __device__ __forceinline__ A transport(const L& u, const A& x) {
+    return Su2<T>::link_as_alg(mul(mul(Su2<T>::dag(u), Su2<T>::alg_as_link(x)), u));
+  }
+};
+
 // components of M + M^dag (hermitian; its traceless part)
 template <typename G> __device__ __forceinline__ typename G::Alg hsum(const typename G::Link& m) {
   typename G::Link h = m;
@@ -98,7 +132,7 @@ __device__ __forceinline__ Alg3<R> hs_herm(const M3<R>& C, const Alg3<R>& y) {
 }
 template <bool LEFT, typename R>
 __device__ __forceinline__ Alg2<R> hs_herm(const Q2<R>& C, const Alg2<R>& y) {
-  using G = Su2<R>;
+  using G = MarchOps<Su2<R>>;
   const Q2<R> Y = G::herm_from_alg(y);
   return hsum<G>(LEFT ? G::mul(Y, C) : G::mul(C, Y));
 }
@@ -171,6 +205,7 @@ template <typename G, typename T, int MODE, bool AL>
 __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2))) k_semi_march(const T* __restrict__ A, const T* __restrict__ B, Geom g,
                                                          MarchIter it, int ncg, int nch, int lz) {
   using L = typename G::Link;
+  using M = MarchOps<G>;
   using Ag = typename G::Alg;
   using R = typename G::Real;
   constexpr int NG = G::NG;
@@ -317,7 +352,7 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
       store_alg(e, (T*)it.Et, d, s, Vp);
       const L w = G::expi(e, (R)-it.madt[d]);
       fence();
-      store_link(G::mul(w, u()), (T*)it.Ut_out, d, s, Vp);
+      store_link(M::mul(w, u()), (T*)it.Ut_out, d, s, Vp);
     }
   };
   // The work of a layer is a sequence of four stages, each its own basic block (a loop that is
@@ -357,11 +392,11 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         ld(u, B, 0, ly, o_t);
         ld(v, B, 1, ly, o_t);
         ld(w, B, 0, ly, o_py);
-        m = G::mul(full(u), pulled(v));
+        m = M::mul(full(u), pulled(v));
         fence();
-        m = G::mul_dag(m, full(w));
+        m = M::mul_dag(m, full(w));
         fence();
-        Ag P = G::proj_mul_dag(m, full(v));
+        Ag P = M::proj_mul_dag(m, full(v));
         tok = P.c[0];
         fence();
         // the loop of slice A alone: MODE 0 forms and stores it, MODE 1 reads it back
@@ -370,11 +405,11 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
           ld(x, A, 0, ly, o_t);
           ld(v, A, 1, ly, o_t);
           ld(w, A, 0, ly, o_py);
-          m = G::mul(full(x), pulled(v));
+          m = M::mul(full(x), pulled(v));
           fence();
-          m = G::mul_dag(m, full(w));
+          m = M::mul_dag(m, full(w));
           fence();
-          m = G::mul_dag(m, full(v));
+          m = M::mul_dag(m, full(v));
           store_link(m, (T*)it.cache, 0, site_z, Vp);
           v = x;
         } else {
@@ -389,28 +424,28 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         Ag gv = fy.get();
         axpy(gv, (R)-it.k[0], hs_herm<true>(m, P));
         fence();
-        axpy(gv, (R)it.k[0], pull_alg(G::transport(full(v), hf), xn.am));
+        axpy(gv, (R)it.k[0], pull_alg(M::transport(full(v), hf), xn.am));
         fy.set(gv);
         tok = gv.c[0];
         fence();
         ld(w, B, 0, ly, o_my);
         ld(v, B, 1, ly, o_my);
-        m = G::mul(full(w), pulled(v));
+        m = M::mul(full(w), pulled(v));
         fence();
-        m = G::mul_dag(m, full(u));
+        m = M::mul_dag(m, full(u));
         fence();
-        P = G::proj_mul_dag(m, full(v));
+        P = M::proj_mul_dag(m, full(v));
         tok = P.c[0];
         fence();
         if constexpr (MODE == 0) {
           ld(u, A, 0, ly, o_my);
           ld(v, A, 1, ly, o_my);
           ld(w, A, 0, ly, o_t);
-          m = G::mul(full(u), pulled(v));
+          m = M::mul(full(u), pulled(v));
           fence();
-          m = G::mul_dag(m, full(w));
+          m = M::mul_dag(m, full(w));
           fence();
-          m = G::mul_dag(m, full(v));
+          m = M::mul_dag(m, full(v));
         } else {
           ld(w, (const T*)it.cache, 0, ly, o_my);
           ld(v, A, 1, ly, o_my);
@@ -419,7 +454,7 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         fence();
         const Ag hb = hs_herm<true>(m, P);
         fence();
-        axpy(fv, (R)-it.k[0], G::transport(full(v), hb));
+        axpy(fv, (R)-it.k[0], M::transport(full(v), hb));
         fx.set(fv);
         tok = fv.c[0];
         break;
@@ -442,23 +477,23 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        cb = G::mul(full(a0), zlx(1));
+        cb = M::mul(full(a0), zlx(1));
         fence();
-        cb = G::mul_dag(cb, full(u));
+        cb = M::mul_dag(cb, full(u));
         fence();
-        cb = G::mul_dag(cb, zl(1));
+        cb = M::mul_dag(cb, zl(1));
         fence();
-        ca = G::mul(full(a0), zlx(0));
+        ca = M::mul(full(a0), zlx(0));
         fence();
-        ca = G::mul_dag(ca, full(u));
+        ca = M::mul_dag(ca, full(u));
         fence();
-        ca = G::mul_dag(ca, zl(0));
+        ca = M::mul_dag(ca, zl(0));
         fence();
         if (!warm) {
           Ag hf = hs_herm<false>(ca, G::proj(cb));
           fx.add((R)it.k[1], hf);
           fence();
-          hf = G::transport(full(a0), hf);   // on the z link at s + e_x
+          hf = M::transport(full(a0), hf);   // on the z link at s + e_x
           fence();
           fz = pull_alg(hf, xn.am);
           hf = hs_herm<false>(cb, G::proj(ca));
@@ -468,12 +503,12 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         Ag cv = hs_herm<true>(ca, G::proj(cb));
         axpy(fz, R(-1), cv);
         fence();
-        cv = G::transport(zl(0), cv);
+        cv = M::transport(zl(0), cv);
         fence();
         {
           const Ag hb = hs_herm<true>(cb, G::proj(ca));
           fence();
-          axpy(cv, R(1), G::transport(zl(1), hb));
+          axpy(cv, R(1), M::transport(zl(1), hb));
         }
         fence();
 #pragma unroll
@@ -486,24 +521,24 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         fence();
         ld(u, B, 0, ly, o_t);
         ld(a0, B, 0, lyp, o_t);
-        cb = G::mul(full(u), zlx(1));
+        cb = M::mul(full(u), zlx(1));
         fence();
-        cb = G::mul_dag(cb, full(a0));
+        cb = M::mul_dag(cb, full(a0));
         fence();
-        const Ag P = G::proj_mul_dag(cb, zl(1));
+        const Ag P = M::proj_mul_dag(cb, zl(1));
         fence();
-        ca = G::mul(full(u), zlx(0));
+        ca = M::mul(full(u), zlx(0));
         fence();
-        ca = G::mul_dag(ca, full(a0));
+        ca = M::mul_dag(ca, full(a0));
         fence();
-        ca = G::mul_dag(ca, zl(0));
+        ca = M::mul_dag(ca, zl(0));
         fence();
         axpy(fz, R(-1), hs_herm<true>(ca, P));
         fence();
         {
           const Ag hf = hs_herm<false>(ca, P);
           fence();
-          axpy(fz, R(1), pull_alg(G::transport(full(u), hf), xn.am));
+          axpy(fz, R(1), pull_alg(M::transport(full(u), hf), xn.am));
         }
 #pragma unroll
         for (int k = 0; k < NG; ++k) fz.c[k] *= (R)it.k[1];
@@ -518,19 +553,19 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         ld(a1, A, 1, ly, o_t);
         ld(v, B, 2, ly, o_py);
         ld(u, A, 1, lyp, o_t);
-        cb = G::mul(full(a1), full(v));
+        cb = M::mul(full(a1), full(v));
         tok = link_token(cb);
         fence();
         ld(v, A, 2, ly, o_py);
-        cb = G::mul_dag(cb, full(u));
+        cb = M::mul_dag(cb, full(u));
         fence();
-        cb = G::mul_dag(cb, zl(1));
+        cb = M::mul_dag(cb, zl(1));
         fence();
-        ca = G::mul(full(a1), full(v));
+        ca = M::mul(full(a1), full(v));
         fence();
-        ca = G::mul_dag(ca, full(u));
+        ca = M::mul_dag(ca, full(u));
         fence();
-        ca = G::mul_dag(ca, zl(0));
+        ca = M::mul_dag(ca, zl(0));
         fence();
         if (!warm) {
           fy.add((R)it.k[2], hs_herm<false>(ca, G::proj(cb)));
@@ -541,12 +576,12 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         Ag cv = hs_herm<true>(ca, G::proj(cb));
         axpy(fz, (R)-it.k[2], cv);
         fence();
-        cv = G::transport(zl(0), cv);
+        cv = M::transport(zl(0), cv);
         fence();
         {
           const Ag hb = hs_herm<true>(cb, G::proj(ca));
           fence();
-          axpy(cv, R(1), G::transport(zl(1), hb));
+          axpy(cv, R(1), M::transport(zl(1), hb));
         }
         fence();
 #pragma unroll
@@ -562,18 +597,18 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         {
           Raw w;
           ld(w, B, 2, ly, o_py);
-          cb = G::mul(full(u), full(w));
+          cb = M::mul(full(u), full(w));
         }
         fence();
-        cb = G::mul_dag(cb, full(a1));
+        cb = M::mul_dag(cb, full(a1));
         fence();
-        const Ag P = G::proj_mul_dag(cb, zl(1));
+        const Ag P = M::proj_mul_dag(cb, zl(1));
         fence();
-        ca = G::mul(full(u), full(v));
+        ca = M::mul(full(u), full(v));
         fence();
-        ca = G::mul_dag(ca, full(a1));
+        ca = M::mul_dag(ca, full(a1));
         fence();
-        ca = G::mul_dag(ca, zl(0));
+        ca = M::mul_dag(ca, zl(0));
         fence();
         const Ag hb = hs_herm<true>(ca, P);
         axpy(fz, (R)-it.k[2], hb);
@@ -587,19 +622,19 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         ld(f0, A, 1, ly, o_my);
         ld(f2, A, 1, lyp, o_my);
         ld(w, B, 2, ly, o_my);
-        m = G::mul(full(f0), zl(1));
+        m = M::mul(full(f0), zl(1));
         fence();
-        m = G::mul_dag(m, full(f2));
+        m = M::mul_dag(m, full(f2));
         tok = link_token(m);
         fence();
         ld(v, A, 2, ly, o_my);
-        Ag P = G::proj_mul_dag(m, full(w));
+        Ag P = M::proj_mul_dag(m, full(w));
         fence();
-        m = G::mul(full(f0), zl(0));
+        m = M::mul(full(f0), zl(0));
         fence();
-        m = G::mul_dag(m, full(f2));
+        m = M::mul_dag(m, full(f2));
         fence();
-        m = G::mul_dag(m, full(v));
+        m = M::mul_dag(m, full(v));
         tok = link_token(m);
         fence();
         Raw g0;
@@ -608,25 +643,25 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
         {
           const Ag hf = hs_herm<false>(m, P);
           fence();
-          axpy(fz, (R)it.k[2], G::transport(full(f0), hf));
+          axpy(fz, (R)it.k[2], M::transport(full(f0), hf));
         }
         fence();
-        m = G::mul(full(g0), zl(1));
+        m = M::mul(full(g0), zl(1));
         fence();
-        m = G::mul_dag(m, full(f2));
+        m = M::mul_dag(m, full(f2));
         fence();
-        P = G::proj_mul_dag(m, full(w));
+        P = M::proj_mul_dag(m, full(w));
         fence();
-        m = G::mul(full(g0), zl(0));
+        m = M::mul(full(g0), zl(0));
         fence();
-        m = G::mul_dag(m, full(f2));
+        m = M::mul_dag(m, full(f2));
         fence();
-        m = G::mul_dag(m, full(v));
+        m = M::mul_dag(m, full(v));
         fence();
         {
           const Ag hf = hs_herm<false>(m, P);
           fence();
-          axpy(fz, (R)it.k[2], G::transport(full(g0), hf));
+          axpy(fz, (R)it.k[2], M::transport(full(g0), hf));
         }
         tok = fz.c[0];
         fence();
