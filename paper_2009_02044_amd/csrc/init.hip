@@ -296,15 +296,6 @@ __device__ __forceinline__ double of_lane(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// all reals of a matrix
-template <typename T> struct FullWidth;
-template <> struct FullWidth<Q2<double>> { static constexpr int value = 4; };
-template <> struct FullWidth<M3<double>> { static constexpr int value = 18; };
-__device__ __forceinline__ double& full_real(Q2<double>& l, int k) { return l.q[k]; }
-__device__ __forceinline__ double& full_real(M3<double>& l, int k) {
-  return k & 1 ? l.im[k / 6][k % 6 / 2] : l.re[k / 6][k % 6 / 2];
-}
-
 // Links and E of one tile of IC_TX x IC_TY transverse sites at one z per work-group.  A transverse link
 // of nucleus N is V_N(x) V_N^dag(x + i), and V_N belongs to a site: each is formed once per tile (and
 // once more per neighbouring tile, on the tile's +x and +y rim) and read from LDS by the threads that

@@ -133,7 +133,7 @@ struct MarchIter {
   void* cache;   // C_xy loops of slice A alone: written by mode 0, read by mode 1
   double k[3], ma[3], madt[3];   // k / 2 of the three planes, -a_d, -a_d dt (set by the launch)
 };
-// elements of the loop cache: one matrix in the stored form of a link per padded site
+// elements of the loop cache: one whole matrix per padded site
 size_t march_cache_elems(const Geom& g, int nc);
 bool march_geometry(const Geom& g);
 template <typename G, typename T>

@@ -224,6 +224,15 @@ template <typename L> struct StoredWidth;
 template <typename T> struct StoredWidth<Q2<T>> { static constexpr int value = 4; };
 template <typename T> struct StoredWidth<M3<T>> { static constexpr int value = SU3_STORED; };
 
+// a matrix by all of its reals, component 2 (3 r + k) + {re, im}
+template <typename L> struct FullWidth;
+template <typename T> struct FullWidth<Q2<T>> { static constexpr int value = 4; };
+template <typename T> struct FullWidth<M3<T>> { static constexpr int value = 18; };
+template <typename T> GL_HD T& full_real(Q2<T>& l, int k) { return l.q[k]; }
+template <typename T> GL_HD T& full_real(M3<T>& l, int k) {
+  return k & 1 ? l.im[k / 6][k % 6 / 2] : l.re[k / 6][k % 6 / 2];
+}
+
 // ---- algebra load / store: f = field base, i = direction (0 for rho) ----------
 template <typename A, typename S>
 GL_HD void load_alg(A& a, const S* __restrict__ f, int i, uint32_t s, int64_t Vp) {

@@ -10,9 +10,9 @@
 //   * links at x + e_z (factor 2 of an (x, z) or (y, z) loop): carried to the next layer;
 //   * links at x + e_y (factor 2 of an (x, y) loop, factor 1 of a (y, z) loop): the site
 //     above forms those loops again at its base - e_y (another wavefront's column).
-// Per site and layer 32 links are loaded (against about 150 when every link forms all its
-// loops), and 71 matrix products are formed (against about 135).  With
-// MODE = 1 the pass also completes the fixed-point iteration of each link as soon as its
+// Per site and layer 30 links are loaded (MODE = 1: 26 and two cached loops; about 150 when every link
+// forms all its loops), and 42 matrix products, 16 derivatives of a loop and 10 transports are formed
+// (MODE = 1).  With MODE = 1 the pass also completes the fixed-point iteration of each link as soon as its
 // force is complete (E' = Ebase + dt f1, under-relaxed, new trial link), so the force is
 // never stored; MODE = 0 stores f1 (the per-step term f1(U(t), U(t - dt))).
 #include <algorithm>
@@ -172,28 +172,31 @@ constexpr int MARCH_SUB = 4, MARCH_WARM = 2;
 //
 // What bounds it: vector memory.  The columns that march at once hold about 30 MB per XCD
 // against 4 MB of L2, so a link that is loaded again in a later stage comes from beyond the L2.
-// So each stage forms every loop of a plane and loads each link it needs once: 32 links and
-// the field per site and layer, 3.5 KB, at 7 TB/s.  With one loop per micro-step (21 of them,
-// 55 links and 5 cached loops, 6.4 KB) an iteration at 512 x 64 x 64 FP64 took 1.51 ms,
-// now 1.06 ms, and the per-step force 1.53 ms, now 0.90 ms (means over a solve's launches).
+// So each stage forms every loop of a plane and loads each link it needs once, but for the z link at y + 1
+// of slice B (stage 2) and, in MODE 0, the site's x link of slice A (stage 0), loaded twice to save
+// registers: an iteration loads 26 links, two loops and the field and guess per site and layer, 3.2 KB
+// for SU(3) FP64, and stores 0.5 KB, at 6.6 TB/s.  With one loop per micro-step (21 of them, 55 links and
+// 5 cached loops, 6.4 KB) an iteration at 512 x 64 x 64 took 1.51 ms, now 1.16 ms (1.13 ms with the loops
+// cut to two rows), and the per-step force 1.53 ms, now 0.92 ms (medians over a solve's launches).
 // Registers: a link is held as stored (24 registers instead of 36) and rebuilt at each use,
 // scheduling fences keep the products of a stage apart, projections are formed from the loops
 // where they are used, and loads take a uniform base and a 32-bit offset.  Without each of
-// these the kernel spilled 100-300 registers.
+// these the kernel spilled 100-300 registers (34 are left in MODE 1, 39 with the general record offsets).
 
 // MarchIter (internal.h): Ebase = E(t - dt/2) + dt f1(U(t), U(t - dt)) (+ dt j on z links);
 // Et the iterate E(t + dt/2), updated in place; Ut_out the new trial links exp(i a dt E') U(t);
 // conv = [max |E' - E_old|, max |E'|] of this iteration (atomic max); F the MODE 0 output;
-// cache: the loops C_xy of slice A alone based at each site, special unitary and stored like
-// links, which MODE 0 stores (it forms them anyway) and the iterations of the step read back
-// (A = U(t) is fixed for the step).  The (x, z) and (y, z) loops of A alone are formed from
-// the links that their stage loads anyway.
+// cache: the loops C_xy of slice A alone based at each site, which MODE 0 stores (it forms them
+// anyway) and the iterations of the step read back (A = U(t) is fixed for the step).  Whole matrices:
+// links are special unitary only up to their storage's rounding, and a third row rebuilt from two
+// leaves the loop's a quarter to a half further off.  The (x, z) and (y, z) loops of A alone are
+// formed from the links that their stage loads anyway.
 
 // Rows of 8 to 64 sites.  A row that leaves lanes idle (33: 31 of 64) still pays: two steps of 2.1 million
 // sites at dt = a_L took 83-89 ms with a kernel per link direction (semi.hip) and take 59 ms at nt =
 // 33, 47-50 ms at 45 and 48, 42 ms at 28 (38 ms at 64).
 bool march_geometry(const Geom& g) { return g.nt >= 8 && g.nt <= 64; }
-size_t march_cache_elems(const Geom& g, int nc) { return (size_t)(nc == 3 ? SU3_STORED : 4) * g.Vp; }
+size_t march_cache_elems(const Geom& g, int nc) { return (size_t)(nc == 3 ? 18 : 4) * g.Vp; }
 
 __device__ __forceinline__ void atomic_max_nn(double* addr, double v) {
   atomicMax((unsigned long long*)addr, (unsigned long long)__double_as_longlong(v));
@@ -277,6 +280,22 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
       for (int k = 0; k < 16 / (int)sizeof(T); ++k) l.v[q * (16 / (int)sizeof(T)) + k] = (R)x[k];
     }
+  };
+  // the cached loop based at in-layer index q of layer z
+  auto ld_loop = [&](L& m, int z, uint32_t q) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(q) : "v"(tok));
+    constexpr int CW = FullWidth<L>::value;
+    R v[CW];
+    load_comps<R, T, CW>(v, (const T*)it.cache, (uint32_t)z * (uint32_t)g.layer + q);
+#pragma unroll
+    for (int k = 0; k < CW; ++k) full_real(m, k) = v[k];
+  };
+  auto keep_loop = [&](L& m, uint32_t s) __attribute__((always_inline)) {
+    constexpr int CW = FullWidth<L>::value;
+    R v[CW];
+#pragma unroll
+    for (int k = 0; k < CW; ++k) v[k] = full_real(m, k);
+    store_comps<R, T, CW>(v, (T*)it.cache, s);
   };
   auto full = [&](Raw& r) __attribute__((always_inline)) -> L {
 #pragma unroll
@@ -410,12 +429,11 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
           m = M::mul_dag(m, full(w));
           fence();
           m = M::mul_dag(m, full(v));
-          store_link(m, (T*)it.cache, 0, site_z, Vp);
+          keep_loop(m, site_z);
           v = x;
         } else {
-          ld(w, (const T*)it.cache, 0, ly, o_t);
+          ld_loop(m, z, t);
           ld(v, A, 0, ly, o_t);
-          m = full(w);
         }
         fence();
         Ag fv = fx.get();   // the carry
@@ -447,9 +465,8 @@ __global__ void __launch_bounds__(MARCH_BS) __attribute__((amdgpu_waves_per_eu(2
           fence();
           m = M::mul_dag(m, full(v));
         } else {
-          ld(w, (const T*)it.cache, 0, ly, o_my);
+          ld_loop(m, z, (uint32_t)(wrap_add(b0.y, -1, g.nt) * g.nt + b0.x));
           ld(v, A, 1, ly, o_my);
-          m = full(w);
         }
         fence();
         const Ag hb = hs_herm<true>(m, P);
@@ -717,8 +734,9 @@ void launch_semi_march(const T* A, const T* B, const Geom& g, const StepConst& c
     it.ma[d] = -c.a[d];
     it.madt[d] = -c.a[d] * c.dt;
   }
-  // work-groups resident at once on 256 CUs, from the kernel's registers: 2 per CU for SU(3) in
-  // double precision, 3 for SU(3) in single and SU(2) in double, 5 for SU(2) in single precision
+  // work-groups at once on 256 CUs: 2 per CU for SU(3) in double precision and 3 in single, from the
+  // kernel's registers; SU(2) 3 and 5, one less than its registers allow (4 in double: two steps of
+  // 200 x 64 x 64 5.43 ms for 4.43, 200 x 33 x 33 3.11 for 2.75)
   constexpr int per_cu = sizeof(T) == 8 ? (G::NC == 3 ? 2 : 3) : (G::NC == 3 ? 3 : 5);
   const int lz = march_chunk(ncg, g.nz, per_cu * 256);
   const int nch = (g.nz + lz - 1) / lz;
