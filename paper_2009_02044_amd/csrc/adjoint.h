@@ -149,7 +149,7 @@ GL_HD typename G::Alg dexp_reverse(const typename G::Alg& e, double c, const typ
       for (int k = 0; k < NG; ++k) t.c[k] = 0.5 * (t.c[k] + y.c[k]);
       X = G::mul(X, X);
     }
-    l = G::transport_inv(X, lam);
+    l = G::transport(G::expi(e, c), lam);   // (X has become e^-2^m b too, but every squaring doubled its error)
   } else {
     const typename G::Alg z = Op::cross(b, t);
 #pragma unroll
