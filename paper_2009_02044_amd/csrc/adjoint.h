@@ -1,7 +1,5 @@
 // Group helpers of the reverse-mode (adjoint) kernels, double precision, host + device.
-// Hermitian matrices H enter products in the form i H: SU(2) a pure quaternion, SU(3) an
-// anti-hermitian 3x3 matrix; G::proj of such a product returns the components of its
-// hermitian part.
+// Products of hermitian traceless matrices are formed from their components (AdjOps).
 #pragma once
 #include "group.h"
 
@@ -14,8 +12,6 @@ namespace gl {
 template <typename G> struct AdjOps;
 template <> struct AdjOps<Su2<double>> {
   using G = Su2<double>;
-  // i X as a pure quaternion
-  static GL_HD G::Link anti(const G::Alg& x) { return G::alg_as_link(x); }
   static GL_HD G::Alg cross(const G::Alg& x, const G::Alg& y) {
     G::Alg z;
     z.c[0] = fmx(x.c[1], y.c[2], -x.c[2] * y.c[1]);
@@ -37,14 +33,6 @@ template <> struct AdjOps<Su2<double>> {
 };
 template <> struct AdjOps<Su3<double>> {
   using G = Su3<double>;
-  static GL_HD G::Link anti(const G::Alg& x) {
-    G::Link h = G::herm(x, 1.0), r;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) { r.re[i][j] = -h.im[i][j]; r.im[i][j] = h.re[i][j]; }
-    return r;
-  }
   // f123 = 1, f147 = f246 = f257 = f345 = 1/2, f156 = f367 = -1/2, f458 = f678 = sqrt(3)/2
   static GL_HD G::Alg cross(const G::Alg& xx, const G::Alg& yy) {
     auto x = [&](int k) { return xx.c[k - 1]; };   // indices 1..8 as in the structure constants

@@ -5,8 +5,8 @@
 // Cotangents (double precision, plain structure of arrays [dir][a][V]):
 //   lam_i(x)  = dL/d eps^a for the left variation U_i(x) -> exp(i eps^a t^a) U_i(x)
 //   ebar_i(x) = dL/dE_i^a(x),  rbarA(x), rbarB(x) = dL/drho^a(x) at lab positions.
-// Hermitian matrices H enter products in the form i H (SU(2): a pure quaternion, SU(3):
-// an anti-hermitian matrix); P(.) of such a product returns its hermitian components.
+// P(M) are the components of the hermitian traceless part of (M - M^dag) / 2i; products of hermitian
+// matrices are formed from their components (adjoint.h).
 //
 // The step  rho' = hop(rho, U);  E' = E + dt (F(U) + j);  U'_i = exp(i c_i E'_i) U_i
 // (c_i = a_i dt) is reversed in three parts:
