@@ -459,10 +459,12 @@ void launch_observe(const T* U, const T* E, const T* rhoA, const T* rhoB, const 
   };
   // SU(2) FP64 spills nothing either way: pinned it takes 122 registers for 144 and a fourth wave per
   // SIMD, but waits for each plane's loads: 200 x 40 x 40 47.9 us pinned, 42.8 us not, 512 x 96 x 96 521 /
-  // 462, with rows in wavefronts 128 x 64 x 64 47.9 / 46.4 and, where the chip stays full longest, 512 x
-  // 64 x 64 164 / 174; with E(t + dt/2) read, 256 x 64 x 64 101 / 84.  (SU(2) FP32 takes the same time.)
+  // 462.  It pays where four waves per SIMD hold the whole pass (140 x 38 x 38 54 / 57, 100 x 30 x 30 18.7 /
+  // 19.3), and with rows in wavefronts where the chip stays full longest (512 x 64 x 64 164 / 174, 128 x 64
+  // x 64 47.9 / 46.4, 256 x 32 x 32 39.1 / 37.6); with E(t + dt/2) read not at all (256 x 64 x 64 101 / 84).
+  // (SU(2) FP32 takes the same time.)
   if constexpr (G::NC == 2 && sizeof(T) == 8) {
-    if (xs && !En && g.V >= (1 << 20)) pick(std::true_type{});
+    if (!En && (xs ? g.V >= (1 << 20) : (int64_t)nbx * g.nz <= 1024)) pick(std::true_type{});
     else pick(std::false_type{});
   } else {
     pick(std::true_type{});
