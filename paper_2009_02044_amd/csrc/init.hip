@@ -49,7 +49,7 @@ size_t ic_work_doubles(const Geom& g, int ng) { return (size_t)6 * 2 * ng * g.la
 // costs five LDS reads for four lines and two outputs, which is what bounds a pass, and no
 // global latency.  Before, every term evaluated its own sincospi, read its datum from memory
 // and all nt columns were formed: 284 us a pass on 16 planes of 192 x 192 (18-20 us on
-// 64 x 64), now 14-28 us (5-10 us).  The table alone, without staging, took 45-76 us: each
+// 64 x 64), now 14-30 us (5-11 us).  The table alone, without staging, took 45-76 us: each
 // term waited for its load.
 // Sums are formed in blocks of DFT_BLOCK terms: a rounding then weighs a block's sum, not the whole
 // line's.  With half a spectrum the errors of +-k no longer cancel, and plain sums have phi 2-5% further
@@ -65,18 +65,25 @@ __device__ __forceinline__ double2 dft_phase(int k, int nt) {
   sincospi(2.0 * (double)k / nt, &w.y, &w.x);
   return w;
 }
-// 1 / (k~^2 + m^2) Theta(Lambda - |k~|)
-__device__ __forceinline__ double dft_filter(int kx, int ky, const DftConst& c) {
-  const double sy = sinpi((double)ky / c.nt), sx = sinpi((double)kx / c.nt);
-  const double k2 = (2.0 / c.a_T) * (2.0 / c.a_T) * (sy * sy + sx * sx);
-  if (c.uv_cut > 0.0 && sqrt(k2) > c.uv_cut) return 0.0;
-  return 1.0 / (k2 + c.m_ir * c.m_ir);
+// sin(pi k / nt) and sin(pi (nt - k) / nt), each as rounded
+struct DftSine {
+  double p, m;
+};
+__device__ __forceinline__ DftSine dft_sine(int k, const DftConst& c) {
+  return DftSine{sinpi((double)k / c.nt), sinpi((double)(k ? c.nt - k : 0) / c.nt)};
 }
-// The weight of a mode of the half spectrum: the mean of the filter at k and -k.  sinpi((nt - k) / nt)
-// rounds away from sinpi(k / nt), so a cut at a mode's |k~| can fall between the two; the real part of
-// the transform then holds half of the mode, along x as along y.
-__device__ __forceinline__ double dft_weight(int kx, int ky, const DftConst& c) {
-  return 0.5 * (dft_filter(kx, ky, c) + dft_filter(kx ? c.nt - kx : 0, ky ? c.nt - ky : 0, c));
+// The weight of a mode (kx, ky) of the half spectrum, and with neg of (kx, -ky): the mean over k and -k of
+// 1 / (k~^2 + m^2) Theta(Lambda - |k~|).  The two sines round differently, so a cut at a mode's |k~| can
+// fall between them; the real part of the transform then holds half of the mode, along x as along y.
+__device__ __forceinline__ double dft_weight(const DftSine& x, const DftSine& y, bool neg, const DftConst& c) {
+  const double yp = neg ? y.m : y.p, ym = neg ? y.p : y.m, a2 = (2.0 / c.a_T) * (2.0 / c.a_T);
+  const double kp = a2 * (yp * yp + x.p * x.p);
+  double w = 1.0;
+  if (c.uv_cut > 0.0) {
+    const double km = a2 * (ym * ym + x.m * x.m);
+    w = (sqrt(kp) > c.uv_cut ? 0.0 : 0.5) + (sqrt(km) > c.uv_cut ? 0.0 : 0.5);
+  }
+  return w / (kp + c.m_ir * c.m_ir);
 }
 // terms 0 .. n - 1 in blocks of B, done() after each
 template <int B, int UNROLL, typename F, typename D>
@@ -174,15 +181,19 @@ k_dft(const double* __restrict__ in, double* __restrict__ out, DftConst c) {
   }
   if (o >= h) return;
   const bool both = MODE != 0 && o != 0 && 2 * o != nt;
+  DftSine sy;
+  if constexpr (MODE == 1) sy = dft_sine(o, c);
 #pragma unroll
   for (int r = 0; r < DFT_LINES; ++r) {
     const int l = l0 + r;
     if (l >= nline) break;
+    DftSine sx;
+    if constexpr (MODE == 1) sx = dft_sine(l, c);
     auto put = [&](int q, double s) {   // output q, its phases c + s i s
       if constexpr (MODE == 3) {
         out[((int64_t)b * nt + l) * nt + q] = fmx(-s, sb[r], sa[r]) / ((double)nt * nt);
       } else {
-        const double f = MODE == 1 ? dft_weight(l, q, c) : 1.0;
+        const double f = MODE == 1 ? dft_weight(sx, sy, q != o, c) : 1.0;
         const int64_t at = ROWS ? ((int64_t)b * nt + l) * h + q : ((int64_t)b * nt + q) * h + l;
         ((double2*)out)[at] = make_double2(f * fmx(-s, sb[r], sa[r]), f * fmx(s, sc[r], sd[r]));
       }
@@ -241,7 +252,7 @@ __global__ void __launch_bounds__(DFT_SMALL_BS) k_dft_small(const double* __rest
         pr += fmx(v.x, w.x, -(v.y * wi));
         pi += fmx(v.x, wi, v.y * w.x);
       }, done);
-      const double q = p == 0 ? dft_weight(x, y, c) : 1.0;
+      const double q = p == 0 ? dft_weight(dft_sine(x, c), dft_sine(y, c), false, c) : 1.0;
       f[1 - p][t] = make_double2(q * sr, q * si);
     }
     __syncthreads();
