@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import synth
-from oracle import lattice, init_mv, observables
+from oracle import lattice, init_mv, observables, su
 from _gpu import (gpu, lattice_or_skip, to_comp, from_comp, field_err, state_errs, mv_setup,
                   new_lattice)
 
@@ -643,6 +643,30 @@ def test_observables_over_partial_sums(nz, nt):
     for k in ("gauss_l2", "rho_l2", "gauss_max"):
         if k in oo:
             assert abs(go[k] - oo[k]) <= 1e-11 * abs(oo[k]) + 1e-14, k
+
+
+@pytest.mark.parametrize("nc,nz,nt", [(2, 129, 49), (2, 129, 48), (2, 128, 49), (2, 5, 49), (2, 2, 200), (3, 33, 33)])
+def test_residual_sums_over_partial_sums(nc, nz, nt):
+    """The sums over all layers, ||G||_2 and ||rho||_2, and max |G| at the same numbers of partial
+    sums, of a state off the Gauss law (where they are not rounding alone).  A site's G is some 60
+    roundings off, each partial sum and the sum over them no more than 40: 1e-12 leaves 40x."""
+    pkg = lattice_or_skip()
+    say("case: residual sums", nc, nz, nt)
+    p = lattice.Params(nc=nc, a_T=4.0, a_L=1.0, dt=0.5)
+    ng = nc * nc - 1
+    st = init_mv.state_from_algebra(synth.normal(800 + nt, (3, nz, nt, nt, ng), 0.6),
+                                    synth.normal(810 + nt, (3, nz, nt, nt, ng), 0.3), p)
+    st.E += su.from_components(synth.normal(820 + nt, (3, nz, nt, nt, ng), 0.3), nc)
+    lat = pkg.Lattice(nc=nc, nz=nz, nt=nt, a_T=4.0, a_L=1.0, dt=0.5, fp=64)
+    lat.init_state(*to_comp(st), step0=0)
+    buf = lat.obs_buffer()
+    lat.observe(buf)
+    o = pkg.Lattice.unpack_obs(buf, nz)
+    rel, gmax = lattice.gauss_residual(st)
+    rho = np.sqrt(np.sum(su.algebra_norm2(st.rhoA + st.rhoB)))
+    for k, ref in (("gauss_l2", rel * rho), ("rho_l2", rho), ("gauss_rel", rel), ("gauss_max", gmax)):
+        assert abs(o[k] - ref) <= 1e-12 * ref, (k, o[k], ref)
+    assert rel > 0.1
 
 
 def _tiled_pair(pkg, nc, fp, nz, nt, reps, seed):

@@ -338,6 +338,13 @@ def test_march_chunk_lengths_agree(nc, nt, nz, reps):
         assert np.array_equal(x, np.broadcast_to(a[k][..., None, :], x.shape)), k
 
 
+@pytest.mark.parametrize("nc,nt,nz,reps", [(3, 21, 10, 60), (2, 21, 10, 90), (3, 63, 3, 16)])
+def test_march_chunks_of_ragged_rows(nc, nt, nz, reps):
+    """Chunks of several layers where rows leave lanes idle, a layer starts inside a storage record
+    and the last column group holds an empty wavefront (21: seven columns of eight; 63)."""
+    test_march_chunk_lengths_agree(nc, nt, nz, reps)
+
+
 @pytest.mark.parametrize("nc,nz,nt,dt", [(3, 5, 9, 1.0), (2, 4, 21, 0.5), (3, 3, 24, 1.0), (2, 3, 33, 1.0), (3, 2, 63, 0.5)])
 def test_march_rows_of_any_length(nc, nz, nt, dt):
     """Rows that do not divide a wavefront (8 < nt < 64): several rows per wavefront with the last
